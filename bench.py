@@ -39,16 +39,23 @@ def log(msg):
 
 
 def fused_bytes_per_node(prec: str, solids: bool) -> int:
-    """Algorithmic HBM bytes of one fused-kernel node update: the 2 x 19
-    populations read and written once, the node's two densities read once, the
-    owner code read once when solids exist."""
+    """Algorithmic HBM bytes of one fluid-kernel node update (every workload
+    here has tau = 1). FP64 runs in moments: seven doubles (two densities,
+    three velocities, two Psi) read and written once. The other forms: the 2 x
+    19 populations read and written once, the node's two densities read once.
+    The owner code is read once when solids exist."""
     s = STORE[prec]
+    if prec == "fp64":
+        return 2 * 7 * s + (4 if solids else 0)
     return 2 * 2 * 19 * s + 2 * RHO[prec] + (4 if solids else 0)
 
 
 def step_bytes_per_node(prec: str) -> int:
-    """Algorithmic bytes of one whole step: populations read and written once
-    plus the two densities written and read once (640 B in FP64)."""
+    """Algorithmic bytes of one whole step: in FP64 the seven moments read and
+    written once; in the other forms populations read and written once plus
+    the two densities written and read once."""
+    if prec == "fp64":
+        return 2 * 7 * STORE[prec]
     return 2 * 2 * 19 * STORE[prec] + 2 * 2 * RHO[prec]
 
 
@@ -88,8 +95,11 @@ def _lattice(s, prec, density=None):
 
 def domain_size_bytes_per_node(prec: str) -> int:
     """Algorithmic bytes of one lb_domain_size call per node: the order
-    parameter pass reads 2 x 19 populations, the owner code and the bounce mask
-    and writes phi (8 B); each of the three line passes reads phi once."""
+    parameter pass reads the two densities and the owner code in FP64, 2 x 19
+    populations, the owner code and the bounce mask in the other forms, and
+    writes phi (8 B); each of the three line passes reads phi once."""
+    if prec == "fp64":
+        return 2 * STORE[prec] + 4 + 8 + 3 * 8
     return 2 * 19 * STORE[prec] + 4 + 4 + 8 + 3 * 8
 
 
@@ -153,7 +163,8 @@ def roofline_of(s, prec, res, traffic):
     per_launch = fused_bytes_per_node(prec, s.n_particles > 0) * s.N
     achieved = per_launch / avg_s / 1e9
     return {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
-            "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": traffic, "kernel": "k_fused",
+            "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": traffic,
+            "kernel": "k_mstep" if prec == "fp64" else "k_fused",
             "algorithmic_bytes_per_launch": per_launch, "avg_launch_ms": round(ms / launches, 5),
             "launches_timed": launches}
 
@@ -165,7 +176,7 @@ def measured_traffic(workload: str, prec: str, kind: str = "fused"):
     if not os.path.exists(path):
         return None
     rec = json.load(open(path))
-    src = os.path.join(ROOT, "paper_1109_3277_amd", "csrc", "lbe_fluid.hip")
+    src = os.path.join(ROOT, "paper_1109_3277_amd", "csrc", "lbe_moment.hip" if prec == "fp64" else "lbe_fluid.hip")
     h = hashlib.sha256(open(src, "rb").read()).hexdigest()[:16]
     if rec.get("source_sha256_16") != h:
         return None

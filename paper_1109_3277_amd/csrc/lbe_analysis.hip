@@ -72,6 +72,22 @@ __global__ __launch_bounds__(kDsThreads) void k_order_param(Box bx, const typena
     if (threadIdx.x == 0) red[(size_t)blockIdx.x * 8 + DS_SUM] = tot[0];
 }
 
+// The same from the moment state (tau = 1).
+__global__ __launch_bounds__(kDsThreads) void k_mom_order_param(Box bx, const double* __restrict__ v,
+                                                                const uint32_t* __restrict__ owner,
+                                                                double* __restrict__ phi, double* __restrict__ red) {
+    const int64_t N = bx.N;
+    double acc[1] = {0.0};
+    for (int64_t n = (int64_t)blockIdx.x * kDsThreads + threadIdx.x; n < N; n += (int64_t)gridDim.x * kDsThreads) {
+        const double p = owner[n] == OWN_FLUID ? v[n] - v[N + n] : 0.0;
+        phi[n] = p;
+        acc[0] += p;
+    }
+    double tot[1];
+    block_sum<1>(acc, tot);
+    if (threadIdx.x == 0) red[(size_t)blockIdx.x * 8 + DS_SUM] = tot[0];
+}
+
 // Ordered sums of the block partials by one block: thread t adds partials
 // t, t + 256, ... in turn, then the fixed tree of block_sum.
 template <int K>
@@ -276,11 +292,16 @@ extern "C" int lb_domain_size(lb_handle* h, double out[8]) {
                                           std::to_string(LB_DOMAIN_MAX_LINE));
     // phi~ is staged in the idle population copy (rewritten by the next step's
     // streaming before anything reads it)
-    double* phi = (double*)h->b.f[1 - h->cur];
-    LBE_AN_DISPATCH(h->prm.precision,
-                    hipLaunchKernelGGL(k_order_param<P>, dim3(kRedBlocks), dim3(kDsThreads), 0, h->stream, h->box,
-                                       (const typename P::S*)h->b.f[h->cur], h->b.owner[h->ocur], h->b.bmask[h->cur],
-                                       phi, h->b.red));
+    // (in moments: what they leave free of it)
+    double* phi = (double*)((char*)h->b.f[1 - h->cur] + (h->mom ? 2 * moment_bytes(&h->prm) : 0));
+    if (h->mom)
+        hipLaunchKernelGGL(k_mom_order_param, dim3(kRedBlocks), dim3(kDsThreads), 0, h->stream, h->box,
+                           h->b.mv[h->mc], h->b.owner[h->ocur], phi, h->b.red);
+    else
+        LBE_AN_DISPATCH(h->prm.precision,
+                        hipLaunchKernelGGL(k_order_param<P>, dim3(kRedBlocks), dim3(kDsThreads), 0, h->stream, h->box,
+                                           (const typename P::S*)h->b.f[h->cur], h->b.owner[h->ocur],
+                                           h->b.bmask[h->cur], phi, h->b.red));
     LBE_HIP_OR_FAIL(h, hipGetLastError());
     hipLaunchKernelGGL(k_ds_mean, dim3(1), dim3(kDsThreads), 0, h->stream, h->b.red, kRedBlocks, (double)h->box.N);
     LBE_HIP_OR_FAIL(h, hipGetLastError());

@@ -61,10 +61,15 @@ void item_capacity(const lb_params& p, size_t cap[BI_COUNT]) {
         tiles_for(p, bx, tx, ty);
         tiles = std::max(tiles, (size_t)tx * ty * p.nz);
     }
+    const size_t np = (size_t)std::max(p.max_particles, 0);
+    const bool mom = in_moments(p);
     cap[BI_NODE] = (N + 255) / 256;
-    cap[BI_TILE] = tiles;
-    cap[BI_TILE_PLAIN] = tiles;
-    cap[BI_PART] = (size_t)std::max(p.max_particles, 0);
+    cap[BI_NODE_POP] = mom ? 0 : cap[BI_NODE];
+    cap[BI_TILE] = cap[BI_TILE_PLAIN] = mom ? 0 : tiles;
+    cap[BI_MTILE] = cap[BI_MTILE_PLAIN] = mom ? tiles : 0;
+    cap[BI_PART] = np;
+    cap[BI_PART_POP] = mom ? 0 : np;
+    cap[BI_PART_MOM] = mom ? np : 0;
 }
 
 struct BatchLayout {
@@ -140,7 +145,11 @@ SysDev sys_dev(const lb_handle* q) {
     d.bmask[0] = q->b.bmask[0];
     d.bmask[1] = q->b.bmask[1];
     d.rec = q->b.rec;
-    d.pfast = q->b.pfast;
+    d.pfast[0] = q->b.pfast[0];
+    d.pfast[1] = q->b.pfast[1];
+    d.mv[0] = q->b.mv[0];
+    d.mv[1] = q->b.mv[1];
+    d.mom = q->mom ? 1 : 0;
     d.kpart = q->b.kpart;
     d.health = q->b.health;
     d.counters = q->b.counters;
@@ -158,6 +167,21 @@ int refresh(lb_handle* h) {
     B->h_sys.resize(nsys);
     B->walls = false;
     for (int k = 0; k < BI_COUNT; k++) B->h_items[k].clear();
+    // systems with tau = 1 go over to moments here
+    int64_t columns = 0;
+    int deep = 1;
+    for (lb_handle* q : B->subs) {
+        if (!in_moments(q->prm)) continue;
+        q->mc = B->parity;
+        const int rc = to_moments(q);
+        if (rc != LB_OK) return fail(h, rc, q->err);
+        int tx, ty;
+        tiles_for(q->prm, B->bx, tx, ty);
+        columns += (int64_t)tx * ty;
+        deep = std::max(deep, (int)q->box.nz);
+    }
+    B->bl.zc = mstep_planes(columns, deep);
+    B->bl.mom = columns > 0;
     for (int s = 0; s < nsys; s++) {
         lb_handle* q = B->subs[s];
         SysDev& d = B->h_sys[s];
@@ -167,9 +191,16 @@ int refresh(lb_handle* h) {
         d.kext = kill_ext(q);
         const int nnode = (int)((q->box.N + 255) / 256);
         const int ntile = d.tiles_x * d.tiles_y * q->box.nz;
+        const int ncol = d.tiles_x * d.tiles_y * ((q->box.nz + B->bl.zc - 1) / B->bl.zc);
         for (int i = 0; i < nnode; i++) B->h_items[BI_NODE].push_back({s, i});
-        for (int i = 0; i < ntile; i++) B->h_items[q->has_solid ? BI_TILE : BI_TILE_PLAIN].push_back({s, i});
         for (int i = 0; i < q->np; i++) B->h_items[BI_PART].push_back({s, i});
+        for (int i = 0; i < q->np; i++) B->h_items[d.mom ? BI_PART_MOM : BI_PART_POP].push_back({s, i});
+        if (d.mom) {
+            for (int i = 0; i < ncol; i++) B->h_items[q->has_solid ? BI_MTILE : BI_MTILE_PLAIN].push_back({s, i});
+        } else {
+            for (int i = 0; i < nnode; i++) B->h_items[BI_NODE_POP].push_back({s, i});
+            for (int i = 0; i < ntile; i++) B->h_items[q->has_solid ? BI_TILE : BI_TILE_PLAIN].push_back({s, i});
+        }
     }
     for (int k = 0; k < BI_COUNT; k++)
         if (B->h_items[k].size() > B->cap_items[k]) return fail(h, LB_EINVAL, "batch work list exceeds its capacity");
@@ -200,11 +231,13 @@ hipError_t enqueue_batch_step(BatchState* B, hipStream_t st, int c) {
     if ((e = launch_batch_shell(bl, prec, st, c)) != hipSuccess) return e;
     if (B->walls && (e = launch_batch_wall_shell(bl, prec, st, c)) != hipSuccess) return e;
     if ((e = launch_batch_fused(bl, prec, st, c, c)) != hipSuccess) return e;
+    if (bl.mom && (e = launch_batch_mstep(bl, st, c)) != hipSuccess) return e;
     if ((e = launch_batch_forces(bl, st)) != hipSuccess) return e;
-    if ((e = launch_batch_bodies(bl, st)) != hipSuccess) return e;
+    if ((e = launch_batch_bodies(bl, st, c)) != hipSuccess) return e;
     if ((e = launch_batch_clear_owner(bl, st, 1 - c)) != hipSuccess) return e;
     if ((e = launch_batch_raster(bl, st, 1 - c)) != hipSuccess) return e;
     if ((e = launch_batch_density(bl, prec, st, 1 - c, 1 - c, c)) != hipSuccess) return e;
+    if (bl.mom && (e = launch_batch_check(bl, (int)B->subs.size(), st, c)) != hipSuccess) return e;
     return launch_batch_killfill(bl, prec, st, c, 1 - c);
 }
 
@@ -282,8 +315,18 @@ int batch_step_async(lb_handle* h, int nsteps) {
     B->last_nodes = (int64_t)nodes;
     B->parity = (c + nsteps) & 1;
     for (lb_handle* q : B->subs) {
-        q->cur = q->ocur = B->parity;
-        q->dens_ready = true;
+        q->ocur = B->parity;
+        if (q->mom) {
+            q->mc = B->parity;
+            q->oprev = 1 - B->parity;
+            q->pops = false;
+            q->acc_prev[0] = q->box.ax;
+            q->acc_prev[1] = q->box.ay;
+            q->acc_prev[2] = q->box.az;
+        } else {
+            q->cur = B->parity;
+            q->dens_ready = true;
+        }
     }
     return LB_OK;
 }
@@ -513,16 +556,27 @@ int lb_batch_tune(lb_handle* h, lb_tune_result* out) {
         LBE_HIP_OR_FAIL(h, hipEventCreate(&e1));
         float best = 0.0f;
         te.bx = B->bx;
+        // (a moment state goes through its populations, which the timed launches
+        // leave alone, and comes back bit for bit)
+        for (lb_handle* q : B->subs) {
+            const int r = to_pops(q);
+            if (r != LB_OK) return fail(h, r, q->err);
+            q->mom = q->mom && !in_moments(q->prm);
+        }
         for (int k = 0; k < LB_TUNE_CANDIDATES && rc == LB_OK; k++) {
             B->bx = kTileWidths[k];
             rc = refresh(h);
             if (rc != LB_OK) break;
             LBE_HIP_OR_FAIL(h, launch_batch_density(B->bl, B->precision, h->stream, c, c, -1));
             LBE_HIP_OR_FAIL(h, launch_batch_shell(B->bl, B->precision, h->stream, c));
-            LBE_HIP_OR_FAIL(h, launch_batch_fused(B->bl, B->precision, h->stream, c, c));
+            auto fluid = [&]() -> hipError_t {
+                const hipError_t e = launch_batch_fused(B->bl, B->precision, h->stream, c, c);
+                return e == hipSuccess && B->bl.mom ? launch_batch_mstep(B->bl, h->stream, c) : e;
+            };
+            LBE_HIP_OR_FAIL(h, fluid());
             LBE_HIP_OR_FAIL(h, hipEventRecord(e0, h->stream));
             constexpr int reps = 3;
-            for (int r = 0; r < reps; r++) LBE_HIP_OR_FAIL(h, launch_batch_fused(B->bl, B->precision, h->stream, c, c));
+            for (int r = 0; r < reps; r++) LBE_HIP_OR_FAIL(h, fluid());
             LBE_HIP_OR_FAIL(h, hipEventRecord(e1, h->stream));
             LBE_HIP_OR_FAIL(h, hipEventSynchronize(e1));
             float ms = 0.0f;
@@ -541,6 +595,7 @@ int lb_batch_tune(lb_handle* h, lb_tune_result* out) {
         for (lb_handle* q : B->subs) {
             const size_t rb = layout_of(&q->prm).rec;
             if (rb) LBE_HIP_OR_FAIL(h, launch_fill_f64(h, q->b.rec, 0.0, (int64_t)(rb / sizeof(double))));
+            LBE_HIP_OR_FAIL(h, launch_fill_u32(h, (uint32_t*)q->b.health + 1, 0u, 1));  // nor has a step been suspect
         }
         std::lock_guard<std::mutex> lk(tune_mutex());
         tune_cache()[key] = te;

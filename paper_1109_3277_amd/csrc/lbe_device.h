@@ -247,19 +247,29 @@ __device__ inline bool particle_box(const Box& bx, const double* part, int cap, 
     return box_of(bx, X, bound_radius(part, cap, p), lo, sz);
 }
 
-// Packed copy of what the fused kernel reads of a particle: kPF doubles per
-// particle (one 128-byte line), centre, velocity, angular velocity and
-// bounding radius, so that a wave reads a particle with one scalar load.
-// Rewritten whenever the particle table changes (body update, placement,
-// state load).
+// Packed copy of what the fluid kernels read of a particle: kPF doubles per
+// particle (one 128-byte line), centre, velocity, angular velocity and record
+// box, so that a wave reads a particle with one scalar load. Rewritten whenever
+// the particle table changes (body update, placement, state load).
 constexpr int kPF = 16;
-enum PFastField : int { PF_X = 0, PF_V = 3, PF_W = 6, PF_RB = 9 };
-__device__ inline void pack_fast(const double* part, int cap, int p, double* __restrict__ pfast) {
+enum PFastField : int { PF_X = 0, PF_V = 3, PF_W = 6, PF_BOX = 9 };
+// The record box: corner and extents along x, y, z (six int32), its bounding box
+// grown by one node on every side, each edge at most the lattice edge; extents 0
+// when the state is not usable. Formed once per particle and step: a wave that
+// forms it for each body it meets spends some 100 vector instructions on it.
+__device__ inline void pack_fast(const Box& bx, const double* part, int cap, int p, double* __restrict__ pfast) {
     double* o = pfast + (size_t)p * kPF;
     const int src[9] = {PX, PY, PZ, VX, VY, VZ, WX, WY, WZ};
     for (int k = 0; k < 9; k++) o[k] = part[src[k] * cap + p];
-    o[PF_RB] = bound_radius(part, cap, p);
-    for (int k = PF_RB + 1; k < kPF; k++) o[k] = 0.0;
+    int* b = (int*)(o + PF_BOX);
+    const int Ls[3] = {bx.nx, bx.ny, bx.nz};
+    int lo[3] = {0, 0, 0}, sz[3] = {0, 0, 0};
+    const bool ok = particle_box(bx, part, cap, p, lo, sz);
+    for (int d = 0; d < 3; d++) {
+        b[d] = ok ? lo[d] - 1 : 0;
+        b[3 + d] = ok ? min(sz[d] + 2, Ls[d]) : 0;
+    }
+    for (int k = PF_BOX + 3; k < kPF; k++) o[k] = 0.0;
 }
 
 // Tiles of the fused kernel: BX x BY nodes of one xy-plane per 256-thread
@@ -282,20 +292,43 @@ constexpr int kPB = 256;
 // the force pass reads and clears them.
 constexpr int kRec = 3;
 
-// Record cell of node xyz for a particle whose bounding box is (lo, sz), or
-// -1 when the node lies outside the record box.
-__device__ inline int rec_cell(const int xyz[3], const int lo[3], const int sz[3], const int Ls[3]) {
-    int off[3], esz[3];
+// Surface velocity V + W x r of a particle (packed copy pq) at node (x, y, z).
+// Multiply-adds written out, so that every kernel forms the same bits.
+__device__ inline double fma_r(double a, double b, double c) { return __builtin_fma(a, b, c); }
+__device__ inline void surface_velocity(const Box& bx, const double* __restrict__ pq, int x, int y, int z, double& ux,
+                                        double& uy, double& uz) {
+#pragma clang fp contract(off)
+    const double rx = minimg((double)x - pq[PF_X], bx.nx), ry = minimg((double)y - pq[PF_X + 1], bx.ny),
+                 rz = minimg((double)z - pq[PF_X + 2], bx.nz);
+    const double wx = pq[PF_W], wy = pq[PF_W + 1], wz = pq[PF_W + 2];
+    ux = pq[PF_V] + fma_r(wy, rz, -(wz * ry));
+    uy = pq[PF_V + 1] + fma_r(wz, rx, -(wx * rz));
+    uz = pq[PF_V + 2] + fma_r(wx, ry, -(wy * rx));
+}
+// Momentum exchange 2 f*_i + C of a link over both components: e the sum of the
+// stored numbers, ref the sum of w_i rho_ref (0 where populations are stored), C
+// the sum of the bounce-back terms.
+template <class L>
+__device__ inline L link_exchange(L e, L ref, L C) {
+#pragma clang fp contract(off)
+    const L f = e + ref;
+    return L(2) * f + C;
+}
+
+// Record cell of node xyz for the particle with packed copy pq, or -1 when the
+// node lies outside the record box.
+__device__ inline int rec_cell(const int xyz[3], const double* __restrict__ pq, const int Ls[3]) {
+    const int* box = (const int*)(pq + PF_BOX);
+    int off[3];
     bool in = true;
 #pragma unroll
     for (int d = 0; d < 3; d++) {
-        int v = xyz[d] - (lo[d] - 1);  // in (-L, 2L) for a centre in [0, L) and rb < L / 2
+        int v = xyz[d] - box[d];  // in (-L, 2L) for a centre in [0, L) and rb < L / 2
         v = v < 0 ? v + Ls[d] : (v >= Ls[d] ? v - Ls[d] : v);
-        esz[d] = min(sz[d] + 2, Ls[d]);
         off[d] = v;
-        in = in && (unsigned)v < (unsigned)esz[d];
+        in = in && (unsigned)v < (unsigned)box[3 + d];
     }
-    return in ? (off[2] * esz[1] + off[1]) * esz[0] + off[0] : -1;
+    return in ? (off[2] * box[4] + off[1]) * box[3] + off[0] : -1;
 }
 
 // Node (ix, iy, iz) of box index t in a box of sz[0] x sz[1] x sz[2].
@@ -351,13 +384,15 @@ struct BoxWalk {
 struct SysDev {
     Box box;
     void* f[2];
+    double* mv[2];   // tau = 1, FP64: moment state copies
+    int mom;         // the system advances in moments
     void* psi;
     void* rho;
     uint32_t* owner[2];
     uint32_t* bmask[2];  // bounce masks of population copy 0 / 1
     double* part;
     double* rec;
-    double* pfast;
+    double* pfast[2];
     double* kpart;
     int* health;
     double* counters;  // [0] fluid mass removed at particle placement

@@ -128,7 +128,7 @@ __global__ __launch_bounds__(256) void k_density(Box bx, const typename P::S* __
 // pass, read by the shell fills) exactly when a lone handle keeps them: the
 // system has solid nodes (particles or walls), Psi is not rho itself, and the
 // workspace holds the buffer.
-__device__ inline void* sys_rho(const SysDev& d) {
+__device__ inline void* sys_rho(const SysDev& d) {  // (systems in populations)
     return (d.rho && (d.np > 0 || d.box.walls != 0) && d.box.psi_kind != 0) ? d.rho : nullptr;
 }
 // Batched: item = (system, block of 256 nodes); populations copy `c`, owner
@@ -409,16 +409,10 @@ __device__ inline void fused_body(const Box& bx, const typename P::S* __restrict
             const int lead = __ffsll(m) - 1;
             const uint32_t q = __builtin_amdgcn_readfirstlane(__shfl(need ? p1 : p2, lead, 64));
             const double* pq = pfast + (size_t)q * kPF;
-            const double qX[3] = {pq[PF_X], pq[PF_X + 1], pq[PF_X + 2]};
-            const double qVx = pq[PF_V], qVy = pq[PF_V + 1], qVz = pq[PF_V + 2];
-            const double qWx = pq[PF_W], qWy = pq[PF_W + 1], qWz = pq[PF_W + 2];
-            const double rx = minimg((double)x - qX[0], nx), ry = minimg((double)y - qX[1], ny),
-                         rz = minimg((double)z - qX[2], nz);
-            const L ux = L(qVx + (qWy * rz - qWz * ry));
-            const L uy = L(qVy + (qWz * rx - qWx * rz));
-            const L uz = L(qVz + (qWx * ry - qWy * rx));
-            int lo[3], sz[3];
-            const int cb = box_of(bx, qX, pq[PF_RB], lo, sz) ? rec_cell(xyz, lo, sz, Ls) : -1;
+            double vx, vy, vz;
+            surface_velocity(bx, pq, x, y, z, vx, vy, vz);
+            const L ux = L(vx), uy = L(vy), uz = L(vz);
+            const int cb = rec_cell(xyz, pq, Ls);
             if (need && p1 == q) {
                 Ux1 = ux;
                 Uy1 = uy;
@@ -454,23 +448,18 @@ __device__ inline void fused_body(const Box& bx, const typename P::S* __restrict
                     int cb = o == p1 ? cb1 : cb2;
                     if (!kDefer && o != p1 && o != p2) {
                         const double* po = pfast + (size_t)o * kPF;
-                        const double X[3] = {po[PF_X], po[PF_X + 1], po[PF_X + 2]};
-                        const double rx = minimg((double)x - X[0], nx);
-                        const double ry = minimg((double)y - X[1], ny);
-                        const double rz = minimg((double)z - X[2], nz);
-                        const double wx = po[PF_W], wy = po[PF_W + 1], wz = po[PF_W + 2];
-                        Ux = L(po[PF_V] + (wy * rz - wz * ry));
-                        Uy = L(po[PF_V + 1] + (wz * rx - wx * rz));
-                        Uz = L(po[PF_V + 2] + (wx * ry - wy * rx));
-                        int lo[3], sz[3];
-                        cb = box_of(bx, X, po[PF_RB], lo, sz) ? rec_cell(xyz, lo, sz, Ls) : -1;
+                        double vx, vy, vz;
+                        surface_velocity(bx, po, x, y, z, vx, vy, vz);
+                        Ux = L(vx);
+                        Uy = L(vy);
+                        Uz = L(vz);
+                        cb = rec_cell(xyz, po, Ls);
                     }
                     const L cu = Ux * L(cx(i)) + Uy * L(cy(i)) + Uz * L(cz(i));
                     C0 = R(L(-6.0 * wq(i)) * cu) * r0;
                     C1 = R(L(-6.0 * wq(i)) * cu) * r1;
-                    // (2 f*_i + C) over both components (f = h + w rho_ref in the deviation forms)
-                    const L fsum = L(f0[i]) + L(f1[i]) + L(P::dev ? wq(i) * (bx.rref[0] + bx.rref[1]) : 0.0);
-                    const L mag = L(2) * fsum + (L(C0) + L(C1));
+                    const L mag = link_exchange<L>(L(f0[i]) + L(f1[i]),
+                                                   L(P::dev ? wq(i) * (bx.rref[0] + bx.rref[1]) : 0.0), L(C0) + L(C1));
                     if (o == p1) {
                         F1[0] += mag * L(cx(i));
                         F1[1] += mag * L(cy(i));
@@ -538,14 +527,9 @@ __device__ inline void fused_body(const Box& bx, const typename P::S* __restrict
                 rare &= ~sel;
                 mine = nxt;
                 const double* po = pfast + (size_t)q * kPF;
-                const double X[3] = {po[PF_X], po[PF_X + 1], po[PF_X + 2]};
-                const double rx = minimg((double)x - X[0], nx);
-                const double ry = minimg((double)y - X[1], ny);
-                const double rz = minimg((double)z - X[2], nz);
-                const double wx = po[PF_W], wy = po[PF_W + 1], wz = po[PF_W + 2];
-                const L Ux = L(po[PF_V] + (wy * rz - wz * ry));
-                const L Uy = L(po[PF_V + 1] + (wz * rx - wx * rz));
-                const L Uz = L(po[PF_V + 2] + (wx * ry - wy * rx));
+                double vx, vy, vz;
+                surface_velocity(bx, po, x, y, z, vx, vy, vz);
+                const L Ux = L(vx), Uy = L(vy), Uz = L(vz);
                 L F[3] = {L(0), L(0), L(0)};
 #pragma unroll
                 for (int i = 1; i < Q; i++) {
@@ -559,15 +543,15 @@ __device__ inline void fused_body(const Box& bx, const typename P::S* __restrict
                         const R v0 = P::raw(*a0), v1 = P::raw(*a1);
                         *a0 = P::mk(v0 + C0);
                         *a1 = P::mk(v1 + C1);
-                        const L fsum = L(v0) + L(v1) + L(P::dev ? wq(i) * (bx.rref[0] + bx.rref[1]) : 0.0);
-                        const L mag = L(2) * fsum + (L(C0) + L(C1));
+                        const L mag = link_exchange<L>(L(v0) + L(v1),
+                                                       L(P::dev ? wq(i) * (bx.rref[0] + bx.rref[1]) : 0.0),
+                                                       L(C0) + L(C1));
                         F[0] += mag * L(cx(i));
                         F[1] += mag * L(cy(i));
                         F[2] += mag * L(cz(i));
                     }
                 }
-                int lo[3], sz[3];
-                const int cb = box_of(bx, X, po[PF_RB], lo, sz) ? rec_cell(xyz, lo, sz, Ls) : -1;
+                const int cb = rec_cell(xyz, po, Ls);
                 if (cb >= 0) {
                     double* r = rec + ((size_t)q * rstride + cb) * kRec;
                     r[0] = F[0];
@@ -598,7 +582,7 @@ __global__ __launch_bounds__(256, sizeof(typename P::R) == 8 ? 2 : (sizeof(typen
     const WorkItem w = items[xcd_remap(blockIdx.x, gridDim.x)];
     const SysDev& d = sd[w.sys];
     fused_body<P, SOLID, BX, BY>(d.box, (const typename P::S*)d.f[c], (typename P::S*)d.f[1 - c],
-                                 (const typename P::R*)d.psi, d.owner[o], d.bmask[c], d.bmask[1 - c], d.pfast, d.rec,
+                                 (const typename P::R*)d.psi, d.owner[o], d.bmask[c], d.bmask[1 - c], d.pfast[o], d.rec,
                                  d.kext * d.kext * d.kext, d.tiles_x, d.tiles_y, w.local, false);
 }
 
@@ -749,11 +733,12 @@ __global__ __launch_bounds__(256) void k_init(Box bx, typename P::S* __restrict_
 }
 
 // ---------------------------------------------------------------- readout
+// Straight into the destination arrays (any may be null).
 template <class P>
 __global__ __launch_bounds__(256) void k_fields(Box bx, const typename P::S* __restrict__ f,
                                                 const uint32_t* __restrict__ owner,
-                                                const uint32_t* __restrict__ bmask, double* __restrict__ out) {
-    using R = typename P::R;
+                                                const uint32_t* __restrict__ bmask, double* __restrict__ ra,
+                                                double* __restrict__ rb, double* __restrict__ u) {
     const int64_t N = bx.N;
     const int64_t n = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (n >= N) return;
@@ -778,11 +763,13 @@ __global__ __launch_bounds__(256) void k_fields(Box bx, const typename P::S* __r
             }
         }
     }
-    out[n] = r[0];
-    out[N + n] = r[1];
+    if (ra) ra[n] = r[0];
+    if (rb) rb[n] = r[1];
     const double rt = r[0] + r[1];
+    if (u) {
 #pragma unroll
-    for (int k = 0; k < 3; k++) out[2 * N + 3 * n + k] = (fluid && rt != 0.0) ? j[k] / rt : 0.0;
+        for (int k = 0; k < 3; k++) u[3 * n + k] = (fluid && rt != 0.0) ? j[k] / rt : 0.0;
+    }
 }
 
 // Owner codes as the ABI reports them: -1 fluid, -2 wall, else the particle index.
@@ -971,7 +958,11 @@ __global__ __launch_bounds__(256) void k_wall_shell_batch(const SysDev* __restri
     const SysDev& d = sd[w.sys];
     if (d.box.walls == 0) return;
     const int64_t n = (int64_t)w.local * 256 + threadIdx.x;
-    if (n < d.box.N) wall_shell_node<R>(d.box, (R*)d.psi, (const R*)sys_rho(d), d.owner[o], n);
+    if (n >= d.box.N) return;
+    if (d.mom)
+        wall_shell_node<double>(d.box, d.mv[o] + 5 * d.box.N, d.mv[o], d.owner[o], n);
+    else
+        wall_shell_node<R>(d.box, (R*)d.psi, (const R*)sys_rho(d), d.owner[o], n);
 }
 // Owner copy cleared for re-rasterisation, wall nodes kept (from the current copy).
 __global__ void k_clear_keep_walls(uint32_t* __restrict__ dst, const uint32_t* __restrict__ cur, int64_t n) {
@@ -1082,11 +1073,11 @@ static void launch_fused_t(lb_handle* h, const Tiles& tl, unsigned grid) {
     const int rstride = ke * ke * ke;
     if (tl.BX == 64)
         hipLaunchKernelGGL((k_fused<P, SOLID, 64, 4>), dim3(grid), dim3(256), 0, h->stream, h->box, fs, fd, ps, ow,
-                           h->b.bmask[h->cur], h->b.bmask[1 - h->cur], h->b.pfast, h->b.rec, rstride, tl.tiles_x,
+                           h->b.bmask[h->cur], h->b.bmask[1 - h->cur], h->b.pfast[h->ocur], h->b.rec, rstride, tl.tiles_x,
                            tl.tiles_y, tl.zrun ? 1 : 0);
     else
         hipLaunchKernelGGL((k_fused<P, SOLID, 32, 8>), dim3(grid), dim3(256), 0, h->stream, h->box, fs, fd, ps, ow,
-                           h->b.bmask[h->cur], h->b.bmask[1 - h->cur], h->b.pfast, h->b.rec, rstride, tl.tiles_x,
+                           h->b.bmask[h->cur], h->b.bmask[1 - h->cur], h->b.pfast[h->ocur], h->b.rec, rstride, tl.tiles_x,
                            tl.tiles_y, tl.zrun ? 1 : 0);
 }
 
@@ -1101,19 +1092,25 @@ hipError_t launch_fused(lb_handle* h) {
     return hipGetLastError();
 }
 
-hipError_t launch_fields(lb_handle* h, double* out) {
+hipError_t launch_fields(lb_handle* h, double* ra, double* rb, double* u) {
+    if (h->mom) return launch_mom_fields(h, ra, rb, u);
     LBE_DISPATCH(h->prm.precision,
                  hipLaunchKernelGGL(k_fields<P>, dim3(nblk(h->box.N)), dim3(256), 0, h->stream, h->box,
                                     (const typename P::S*)h->b.f[h->cur], h->b.owner[h->ocur], h->b.bmask[h->cur],
-                                    out));
+                                    ra, rb, u));
     return hipGetLastError();
 }
 
 hipError_t launch_stats(lb_handle* h) {
-    LBE_DISPATCH(h->prm.precision,
+    if (h->mom) {
+        const hipError_t e = launch_mom_stats(h);
+        if (e != hipSuccess) return e;
+    } else {
+        LBE_DISPATCH(h->prm.precision,
                  hipLaunchKernelGGL(k_stats_partial<P>, dim3(kRedBlocks), dim3(256), 0, h->stream, h->box,
                                     (const typename P::S*)h->b.f[h->cur], h->b.owner[h->ocur], h->b.bmask[h->cur],
                                     h->b.red));
+    }
     hipLaunchKernelGGL(k_stats_final, dim3(1), dim3(64), 0, h->stream, h->b.red, kRedBlocks);
     return hipGetLastError();
 }
@@ -1149,13 +1146,12 @@ hipError_t launch_fill_u32(lb_handle* h, uint32_t* p, uint32_t v, int64_t n) {
 }
 hipError_t launch_wall_shell(lb_handle* h) {
     if (!h->box.walls) return hipSuccess;
-    const void* rho = (h->has_solid && h->prm.psi_kind != 0) ? h->b.rho : nullptr;
     if (h->prm.precision == LB_FP64)
         hipLaunchKernelGGL(k_wall_shell<double>, dim3(nblk(h->box.N)), dim3(256), 0, h->stream, h->box,
-                           (double*)h->b.psi, (const double*)rho, h->b.owner[h->ocur]);
+                           (double*)psi_now(h), (const double*)rho_now(h), h->b.owner[h->ocur]);
     else
         hipLaunchKernelGGL(k_wall_shell<float>, dim3(nblk(h->box.N)), dim3(256), 0, h->stream, h->box,
-                           (float*)h->b.psi, (const float*)rho, h->b.owner[h->ocur]);
+                           (float*)psi_now(h), (const float*)rho_now(h), h->b.owner[h->ocur]);
     return hipGetLastError();
 }
 hipError_t launch_batch_wall_shell(const BatchLaunch& bl, int precision, hipStream_t st, int o) {
@@ -1194,9 +1190,9 @@ size_t rho_elem_bytes(int precision) { return precision == LB_FP64 ? 8 : 4; }
 // ---------------------------------------------------------------- batched launchers
 
 hipError_t launch_batch_density(const BatchLaunch& bl, int precision, hipStream_t st, int c, int o, int oo) {
-    if (bl.n[BI_NODE] == 0) return hipSuccess;
-    LBE_DISPATCH(precision, hipLaunchKernelGGL(k_density_batch<P>, dim3(bl.n[BI_NODE]), dim3(256), 0, st, bl.sys,
-                                               bl.items[BI_NODE], c, o, oo));
+    if (bl.n[BI_NODE_POP] == 0) return hipSuccess;
+    LBE_DISPATCH(precision, hipLaunchKernelGGL(k_density_batch<P>, dim3(bl.n[BI_NODE_POP]), dim3(256), 0, st, bl.sys,
+                                               bl.items[BI_NODE_POP], c, o, oo));
     return hipGetLastError();
 }
 

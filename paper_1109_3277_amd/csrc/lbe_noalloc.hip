@@ -11,6 +11,7 @@
 #include <mutex>
 
 #include "lbe_internal.h"
+#include "lbe_moment.h"
 
 namespace lbe {
 namespace {
@@ -44,9 +45,10 @@ hipError_t scratch_of(int dev, double** out) {
 
 // Partial sums of block b (of kNB) of system s over its nodes n = b * 256 +
 // t, b * 256 + t + kNB * 256, ...: masses, momentum, fluid count (sums) and
-// the health flag (max), into part8[0..7]. Populations copy c, owner copy o.
+// the health flag (max), into part8[0..7]. Populations copy c (or moment copy m),
+// owner copy o.
 template <class P>
-__device__ void stats_partial(const SysDev& d, int c, int o, int b, double* __restrict__ part8) {
+__device__ void stats_partial(const SysDev& d, int c, int m, int o, int b, double* __restrict__ part8) {
     using S = typename P::S;
     const Box& bx = d.box;
     const int64_t N = bx.N;
@@ -54,7 +56,11 @@ __device__ void stats_partial(const SysDev& d, int c, int o, int b, double* __re
     const uint32_t* owner = d.owner[o];
     const uint32_t* bmask = d.bmask[c];
     double acc[7] = {0, 0, 0, 0, 0, 0, 0};
-    for (int64_t n = (int64_t)b * 256 + threadIdx.x; n < N; n += (int64_t)kNB * 256) {
+    if (d.mom) {
+        mom_stats_acc(bx, d.mv[m], owner, (int64_t)b * 256 + threadIdx.x, (int64_t)kNB * 256, acc);
+        acc[6] = acc[6] > 0.0 ? 1.0 : 0.0;
+    }
+    for (int64_t n = d.mom ? N : (int64_t)b * 256 + threadIdx.x; n < N; n += (int64_t)kNB * 256) {
         if (owner[n] != OWN_FLUID) continue;
         acc[5] += 1.0;
         const uint32_t bm = bmask[n];
@@ -99,11 +105,11 @@ __device__ void stats_partial(const SysDev& d, int c, int o, int b, double* __re
 template <class P>
 __global__ __launch_bounds__(256) void k_stats_nb_batch(const SysDev* __restrict__ sd, int c, double* __restrict__ sc) {
     const int s = blockIdx.y, b = blockIdx.x;
-    stats_partial<P>(sd[s], c, c, b, sc + ((size_t)s * kNB + b) * 8);
+    stats_partial<P>(sd[s], c, c, c, b, sc + ((size_t)s * kNB + b) * 8);
 }
 template <class P>
-__global__ __launch_bounds__(256) void k_stats_nb_one(SysDev d, int c, int o, double* __restrict__ sc) {
-    stats_partial<P>(d, c, o, blockIdx.x, sc + (size_t)blockIdx.x * 8);
+__global__ __launch_bounds__(256) void k_stats_nb_one(SysDev d, int c, int m, int o, double* __restrict__ sc) {
+    stats_partial<P>(d, c, m, o, blockIdx.x, sc + (size_t)blockIdx.x * 8);
 }
 
 // Totals of system s in the order lb_stats forms them: partials in block
@@ -179,7 +185,7 @@ extern "C" int lb_stats_noalloc(lb_handle* h, double* dev_out) {
     if (!h->inited) return fail(h, LB_ESTATE, "fields not initialised");
     const SysDev d = sys_dev(h);
     LBE_NA_DISPATCH(h->prm.precision, hipLaunchKernelGGL(k_stats_nb_one<P>, dim3(kNB), dim3(256), 0, h->stream, d,
-                                                          h->cur, h->ocur, sc));
+                                                          h->cur, h->mc, h->ocur, sc));
     LBE_HIP_OR_FAIL(h, hipGetLastError());
     hipLaunchKernelGGL(k_stats_final_one, dim3(1), dim3(64), 0, h->stream, d, sc, dev_out);
     LBE_HIP_OR_FAIL(h, hipGetLastError());

@@ -13,6 +13,7 @@
 #include <algorithm>
 
 #include "lbe_internal.h"
+#include "lbe_moment.h"
 
 namespace lbe {
 
@@ -235,7 +236,8 @@ __device__ inline void shell_body(const Box& bx, R* __restrict__ psi, const R* _
 template <class R>
 __global__ __launch_bounds__(kPB) void k_shell(Box bx, R* __restrict__ psi, const R* __restrict__ rho,
                                                const uint32_t* __restrict__ owner, const double* __restrict__ part,
-                                               int cap) {
+                                               int cap, int* __restrict__ suspect) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) *suspect = 0;  // of the step that begins
     shell_body<R>(bx, psi, rho, owner, part, cap, blockIdx.x);
 }
 template <class R>
@@ -243,7 +245,10 @@ __global__ __launch_bounds__(kPB) void k_shell_batch(const SysDev* __restrict__ 
                                                      int o) {
     const WorkItem w = items[blockIdx.x];
     const SysDev& d = sd[w.sys];
-    shell_body<R>(d.box, (R*)d.psi, (const R*)d.rho, d.owner[o], d.part, d.cap, w.local);
+    if (d.mom)
+        shell_body<double>(d.box, d.mv[o] + 5 * d.box.N, d.mv[o], d.owner[o], d.part, d.cap, w.local);
+    else
+        shell_body<R>(d.box, (R*)d.psi, (const R*)d.rho, d.owner[o], d.part, d.cap, w.local);
 }
 
 // ---------------------------------------------------------------- S6 forces
@@ -456,7 +461,7 @@ __device__ inline void bodies_body(const Box& bx, double* __restrict__ part, int
     F_(QY) = nyq / nn;
     F_(QZ) = nzq / nn;
 #undef F_
-    pack_fast(part, cap, p, pfast);
+    pack_fast(bx, part, cap, p, pfast);
 }
 __global__ __launch_bounds__(64) void k_bodies(Box bx, double* __restrict__ part, int cap,
                                                const double* __restrict__ kpart, int nk,
@@ -464,16 +469,16 @@ __global__ __launch_bounds__(64) void k_bodies(Box bx, double* __restrict__ part
     bodies_body(bx, part, cap, kpart, nk, pfast, blockIdx.x);
 }
 __global__ __launch_bounds__(64) void k_bodies_batch(const SysDev* __restrict__ sd,
-                                                     const WorkItem* __restrict__ items) {
+                                                     const WorkItem* __restrict__ items, int o) {
     const WorkItem w = items[blockIdx.x];
     const SysDev& d = sd[w.sys];
-    bodies_body(d.box, d.part, d.cap, d.kpart, 1, d.pfast, w.local);
+    bodies_body(d.box, d.part, d.cap, d.kpart, 1, d.pfast[1 - o], w.local);
 }
 
 // Packed particle table of particles [0, np) from the particle table.
-__global__ void k_pack_fast(const double* __restrict__ part, int cap, int np, double* __restrict__ pfast) {
+__global__ void k_pack_fast(Box bx, const double* __restrict__ part, int cap, int np, double* __restrict__ pfast) {
     const int p = blockIdx.x * blockDim.x + threadIdx.x;
-    if (p < np) pack_fast(part, cap, p, pfast);
+    if (p < np) pack_fast(bx, part, cap, p, pfast);
 }
 
 // Pending kill/fill impulses: add the partial slots into the particle's J, H
@@ -494,6 +499,7 @@ __global__ void k_fold_impulses(double* __restrict__ part, int cap, int np, doub
 // ---------------------------------------------------------------- S8
 template <class R>
 __device__ inline R feq_p(int i, R rho, R ux, R uy, R uz) {
+#pragma clang fp contract(off)
     const R uu = ux * ux + uy * uy + uz * uz;
     const R cu = R(cx(i)) * ux + R(cy(i)) * uy + R(cz(i)) * uz;
     return R(wq(i)) * rho * (R(1) + R(3) * cu + R(4.5) * cu * cu - R(1.5) * uu);
@@ -522,6 +528,7 @@ __device__ inline void killfill_node(const Box& bx, typename P::S* __restrict__ 
                                      typename P::R* __restrict__ rho, const double* __restrict__ part, int cap, int p,
                                      bool kill, int x, int y, int z, int64_t n, const double (&Xn)[3],
                                      double (&acc)[8]) {
+#pragma clang fp contract(off)  // the same bits in the lone and the batched kernel
     using R = typename P::R;
     const int64_t N = bx.N;
     const int Ls[3] = {bx.nx, bx.ny, bx.nz};
@@ -636,13 +643,69 @@ __device__ inline void killfill_node(const Box& bx, typename P::S* __restrict__ 
     for (int k = 0; k < 8; k++) acc[k] += d[k];
 }
 
-template <class P>
-__device__ inline void killfill_body(const Box& bx, typename P::S* __restrict__ f,
-                                     const uint32_t* __restrict__ own_old, const uint32_t* __restrict__ own_new,
-                                     uint32_t* __restrict__ bmask, typename P::R* __restrict__ psi,
-                                     typename P::R* __restrict__ rho,
-                                     const double* __restrict__ part, int cap, int kext, double* __restrict__ kpart,
-                                     int* __restrict__ health, int p) {
+// The same in moments (lbe_moment.h): v the new copy, v0 the one before. A kill
+// takes the node's momentum and mass from its seven numbers; a fill leaves the
+// node's populations at f^eq(rho_new^c, u), of which only the sums are kept,
+// and their densities and velocity in the node's place of v0 (not read there
+// any more), from which a checkpoint forms the populations again.
+__device__ inline void killfill_mom_node(const Box& bx, double* __restrict__ v, double* __restrict__ v0,
+                                         const uint32_t* __restrict__ own_old, const uint32_t* __restrict__ own_new,
+                                         const double* __restrict__ part, int cap, int p, bool kill, int x, int y, int z,
+                                         int64_t n, const double (&Xn)[3], double (&acc)[8]) {
+#pragma clang fp contract(off)
+    const int64_t N = bx.N;
+    const int Ls[3] = {bx.nx, bx.ny, bx.nz};
+    const double r[3] = {minimg((double)x - Xn[0], Ls[0]), minimg((double)y - Xn[1], Ls[1]),
+                         minimg((double)z - Xn[2], Ls[2])};
+    double j[3], m;
+    if (kill) {
+        m = v[n] + v[N + n];
+        for (int d = 0; d < 3; d++) j[d] = m != 0.0 ? m * v[(2 + d) * N + n] : 0.0;
+    } else {
+        const double V[3] = {part[VX * cap + p], part[VY * cap + p], part[VZ * cap + p]};
+        const double W[3] = {part[WX * cap + p], part[WY * cap + p], part[WZ * cap + p]};
+        double rn[2] = {0.0, 0.0};
+        int cnt = 0;
+        uint32_t both[Q];
+        double d0[Q], d1[Q];
+#pragma unroll
+        for (int i = 1; i < Q; i++) {
+            const int64_t e = node_index(bx, wrapc(x + cx(i), Ls[0]), wrapc(y + cy(i), Ls[1]), wrapc(z + cz(i), Ls[2]));
+            both[i] = own_old[e] & own_new[e];  // all ones only where both are fluid
+            d0[i] = v[e];
+            d1[i] = v[N + e];
+        }
+#pragma unroll
+        for (int i = 1; i < Q; i++) {
+            if (both[i] != OWN_FLUID) continue;
+            rn[0] += d0[i];
+            rn[1] += d1[i];
+            cnt++;
+        }
+        for (int c = 0; c < 2; c++) rn[c] = cnt > 0 ? rn[c] / (double)cnt : bx.rmean0[c];
+        const double ub[3] = {V[0] + (W[1] * r[2] - W[2] * r[1]), V[1] + (W[2] * r[0] - W[0] * r[2]),
+                              V[2] + (W[0] * r[1] - W[1] * r[0])};
+        double out[kMomPlanes];
+        fill_node(bx, rn[0], rn[1], ub, out);
+#pragma unroll
+        for (int k = 0; k < kMomPlanes; k++) v[(size_t)k * N + n] = out[k];
+        v0[n] = rn[0];
+        v0[N + n] = rn[1];
+        for (int d = 0; d < 3; d++) v0[(2 + d) * N + n] = ub[d];
+        m = rn[0] + rn[1];
+        for (int d = 0; d < 3; d++) j[d] = -m * ub[d];
+    }
+    const double d[8] = {j[0], j[1], j[2], r[1] * j[2] - r[2] * j[1], r[2] * j[0] - r[0] * j[2],
+                         r[0] * j[1] - r[1] * j[0], kill ? m : 0.0, kill ? 0.0 : m};
+#pragma unroll
+    for (int k = 0; k < 8; k++) acc[k] += d[k];
+}
+
+// `node(kill, x, y, z, n, Xn, acc)` handles one changing node.
+template <class Node>
+__device__ inline void killfill_body(const Box& bx, const uint32_t* __restrict__ own_old,
+                                     const uint32_t* __restrict__ own_new, const double* __restrict__ part, int cap,
+                                     int kext, double* __restrict__ kpart, int* __restrict__ health, int p, Node node) {
     const int Ls[3] = {bx.nx, bx.ny, bx.nz};
     double acc[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};  // J, H, killed mass, filled mass
     int lo[3] = {0, 0, 0}, sz[3] = {0, 0, 0};
@@ -704,8 +767,7 @@ __device__ inline void killfill_body(const Box& bx, typename P::S* __restrict__ 
             box_node(base + k * kPB + threadIdx.x, sz, ix, iy, iz);
             const int x = wrapc_any(lo[0] + ix, Ls[0]), y = wrapc_any(lo[1] + iy, Ls[1]),
                       z = wrapc_any(lo[2] + iz, Ls[2]);
-            killfill_node<P>(bx, f, own_old, own_new, bmask, psi, rho, part, cap, p, b == 1u, x, y, z,
-                             node_index(bx, x, y, z), Xn, acc);
+            node(b == 1u, x, y, z, node_index(bx, x, y, z), Xn, acc);
         }
     }
     double tot[8];
@@ -720,7 +782,12 @@ __global__ __launch_bounds__(kPB, 3) void k_killfill(Box bx, typename P::S* __re
                                                   typename P::R* __restrict__ psi, typename P::R* __restrict__ rho,
                                                   const double* __restrict__ part, int cap, int kext,
                                                   double* __restrict__ kpart, int* __restrict__ health) {
-    killfill_body<P>(bx, f, own_old, own_new, bmask, psi, rho, part, cap, kext, kpart, health, blockIdx.x);
+    const int p = blockIdx.x;
+    killfill_body(bx, own_old, own_new, part, cap, kext, kpart, health, p,
+                  [&](bool kill, int x, int y, int z, int64_t n, const double(&Xn)[3], double(&acc)[8]) {
+                      killfill_node<P>(bx, f, own_old, own_new, bmask, psi, rho, part, cap, p, kill, x, y, z, n, Xn,
+                                       acc);
+                  });
 }
 // Batched: item = (system, particle); owner copy `oo` is the old map, 1 - oo
 // the new one; populations copy `fd`.
@@ -729,8 +796,38 @@ __global__ __launch_bounds__(kPB, 3) void k_killfill_batch(const SysDev* __restr
                                                         const WorkItem* __restrict__ items, int oo, int fd) {
     const WorkItem w = items[blockIdx.x];
     const SysDev& d = sd[w.sys];
-    killfill_body<P>(d.box, (typename P::S*)d.f[fd], d.owner[oo], d.owner[1 - oo], d.bmask[fd], (typename P::R*)d.psi,
-                     (typename P::R*)d.rho, d.part, d.cap, d.kext, d.kpart, d.health, w.local);
+    const int p = w.local;
+    killfill_body(d.box, d.owner[oo], d.owner[1 - oo], d.part, d.cap, d.kext, d.kpart, d.health, p,
+                  [&](bool kill, int x, int y, int z, int64_t n, const double(&Xn)[3], double(&acc)[8]) {
+                      killfill_node<P>(d.box, (typename P::S*)d.f[fd], d.owner[oo], d.owner[1 - oo], d.bmask[fd],
+                                       (typename P::R*)d.psi, (typename P::R*)d.rho, d.part, d.cap, p, kill, x, y, z, n,
+                                       Xn, acc);
+                  });
+}
+// In moments: v the new copy, v0 the one before.
+__global__ __launch_bounds__(kPB, 3) void k_killfill_mom(Box bx, double* __restrict__ v, double* __restrict__ v0,
+                                                         const uint32_t* __restrict__ own_old,
+                                                         const uint32_t* __restrict__ own_new,
+                                                         const double* __restrict__ part, int cap, int kext,
+                                                         double* __restrict__ kpart, int* __restrict__ health) {
+    const int p = blockIdx.x;
+    // (filled nodes are not fluid in own_old: the check and the fills do not meet)
+    check_suspect(bx, v, own_old, own_new, health + 1, health, p, gridDim.x);
+    killfill_body(bx, own_old, own_new, part, cap, kext, kpart, health, p,
+                  [&](bool kill, int x, int y, int z, int64_t n, const double(&Xn)[3], double(&acc)[8]) {
+                      killfill_mom_node(bx, v, v0, own_old, own_new, part, cap, p, kill, x, y, z, n, Xn, acc);
+                  });
+}
+__global__ __launch_bounds__(kPB, 3) void k_killfill_mom_batch(const SysDev* __restrict__ sd,
+                                                               const WorkItem* __restrict__ items, int c) {
+    const WorkItem w = items[blockIdx.x];
+    const SysDev& d = sd[w.sys];
+    const int p = w.local;
+    killfill_body(d.box, d.owner[c], d.owner[1 - c], d.part, d.cap, d.kext, d.kpart, d.health, p,
+                  [&](bool kill, int x, int y, int z, int64_t n, const double(&Xn)[3], double(&acc)[8]) {
+                      killfill_mom_node(d.box, d.mv[1 - c], d.mv[c], d.owner[c], d.owner[1 - c], d.part, d.cap, p, kill,
+                                        x, y, z, n, Xn, acc);
+                  });
 }
 
 // ---------------------------------------------------------------- launchers
@@ -751,11 +848,13 @@ int kill_ext(const lb_handle* h) { return killfill_extent(h->box.nx, h->box.ny, 
 hipError_t launch_shell(lb_handle* h) {
     if (h->np <= 0) return hipSuccess;
     if (h->prm.precision == LB_FP64)
-        hipLaunchKernelGGL(k_shell<double>, dim3(h->np), dim3(kPB), 0, h->stream, h->box, (double*)h->b.psi,
-                           (const double*)h->b.rho, h->b.owner[h->ocur], h->b.part, h->cap);
+        hipLaunchKernelGGL(k_shell<double>, dim3(h->np), dim3(kPB), 0, h->stream, h->box, (double*)psi_now(h),
+                           (const double*)(h->mom ? rho_now(h) : h->b.rho), h->b.owner[h->ocur], h->b.part, h->cap,
+                           h->b.health + 1);
     else
-        hipLaunchKernelGGL(k_shell<float>, dim3(h->np), dim3(kPB), 0, h->stream, h->box, (float*)h->b.psi,
-                           (const float*)h->b.rho, h->b.owner[h->ocur], h->b.part, h->cap);
+        hipLaunchKernelGGL(k_shell<float>, dim3(h->np), dim3(kPB), 0, h->stream, h->box, (float*)psi_now(h),
+                           (const float*)(h->mom ? rho_now(h) : h->b.rho), h->b.owner[h->ocur], h->b.part, h->cap,
+                           h->b.health + 1);
     return hipGetLastError();
 }
 
@@ -769,13 +868,13 @@ hipError_t launch_forces(lb_handle* h) {
 hipError_t launch_bodies(lb_handle* h) {
     if (h->np <= 0) return hipSuccess;
     hipLaunchKernelGGL(k_bodies, dim3(h->np), dim3(64), 0, h->stream, h->box, h->b.part, h->cap, h->b.kpart, 1,
-                       h->b.pfast);
+                       h->b.pfast[1 - h->ocur]);  // belongs to the owner map about to be drawn
     return hipGetLastError();
 }
 hipError_t launch_pack_fast(lb_handle* h) {
     if (h->np <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_pack_fast, dim3((h->np + 255) / 256), dim3(256), 0, h->stream, h->b.part, h->cap, h->np,
-                       h->b.pfast);
+    hipLaunchKernelGGL(k_pack_fast, dim3((h->np + 255) / 256), dim3(256), 0, h->stream, h->box, h->b.part, h->cap, h->np,
+                       h->b.pfast[h->ocur]);
     return hipGetLastError();
 }
 
@@ -800,6 +899,11 @@ hipError_t launch_killfill(lb_handle* h) {
     uint32_t* on = h->b.owner[1 - h->ocur];
     void* fn = h->b.f[1 - h->cur];
     const int kext = kill_ext(h);
+    if (h->mom) {
+        hipLaunchKernelGGL(k_killfill_mom, dim3(h->np), dim3(kPB), 0, h->stream, h->box, h->b.mv[1 - h->mc],
+                           h->b.mv[h->mc], oo, on, h->b.part, h->cap, kext, h->b.kpart, h->b.health);
+        return hipGetLastError();
+    }
     LBE_PDISPATCH(h->prm.precision,
                   hipLaunchKernelGGL(k_killfill<P>, dim3(h->np), dim3(kPB), 0, h->stream, h->box,
                                      (typename P::S*)fn, oo, on, h->b.bmask[1 - h->cur], (typename P::R*)h->b.psi,
@@ -825,9 +929,9 @@ hipError_t launch_batch_forces(const BatchLaunch& bl, hipStream_t st) {
     return hipGetLastError();
 }
 
-hipError_t launch_batch_bodies(const BatchLaunch& bl, hipStream_t st) {
+hipError_t launch_batch_bodies(const BatchLaunch& bl, hipStream_t st, int o) {
     if (bl.n[BI_PART] == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_bodies_batch, dim3(bl.n[BI_PART]), dim3(64), 0, st, bl.sys, bl.items[BI_PART]);
+    hipLaunchKernelGGL(k_bodies_batch, dim3(bl.n[BI_PART]), dim3(64), 0, st, bl.sys, bl.items[BI_PART], o);
     return hipGetLastError();
 }
 
@@ -838,9 +942,12 @@ hipError_t launch_batch_raster(const BatchLaunch& bl, hipStream_t st, int o) {
 }
 
 hipError_t launch_batch_killfill(const BatchLaunch& bl, int precision, hipStream_t st, int oo, int fd) {
-    if (bl.n[BI_PART] == 0) return hipSuccess;
-    LBE_PDISPATCH(precision, hipLaunchKernelGGL(k_killfill_batch<P>, dim3(bl.n[BI_PART]), dim3(kPB), 0, st, bl.sys,
-                                                bl.items[BI_PART], oo, fd));
+    if (bl.n[BI_PART_POP] > 0)
+        LBE_PDISPATCH(precision, hipLaunchKernelGGL(k_killfill_batch<P>, dim3(bl.n[BI_PART_POP]), dim3(kPB), 0, st,
+                                                    bl.sys, bl.items[BI_PART_POP], oo, fd));
+    if (bl.n[BI_PART_MOM] > 0)
+        hipLaunchKernelGGL(k_killfill_mom_batch, dim3(bl.n[BI_PART_MOM]), dim3(kPB), 0, st, bl.sys,
+                           bl.items[BI_PART_MOM], oo);
     return hipGetLastError();
 }
 

@@ -65,15 +65,19 @@ Layout layout_of(const lb_params* p) {
     L.kpart = align_up(cap * 8 * sizeof(double));
     L.red = align_up((kRedBlocks + 1) * 8 * sizeof(double));
     L.counters = align_up(8 * sizeof(double));
-    L.health = align_up(sizeof(int));
+    L.health = align_up(2 * sizeof(int));
     // pair cell list: counts and starts of at most kMaxCellsPerAxis^3 cells
     // (one cell per node at most), the cell of each particle and the list
     size_t ncell = 1;
     for (int d : {p->nx, p->ny, p->nz}) ncell *= (size_t)std::min(d, kMaxCellsPerAxis);
     L.cells = p->max_particles > 1 ? align_up((2 * ncell + 1 + 2 * cap) * sizeof(int)) : 0;
-    L.total = 2 * L.f + L.psi + L.rho + 2 * L.owner + 2 * L.bmask + L.part + L.pfast + L.rec + L.kpart + L.red +
+    L.total = 2 * L.f + L.psi + L.rho + 2 * L.owner + 2 * L.bmask + L.part + 2 * L.pfast + L.rec + L.kpart + L.red +
               L.counters + L.health + L.cells;
     return L;
+}
+
+size_t moment_bytes(const lb_params* p) {
+    return align_up((size_t)kMomPlanes * p->nx * p->ny * p->nz * sizeof(double));
 }
 
 int setup_handle(lb_handle* h, const lb_params* prm, char* ws, size_t ws_bytes, hipStream_t stream) {
@@ -105,6 +109,10 @@ int setup_handle(lb_handle* h, const lb_params* prm, char* ws, size_t ws_bytes, 
     char* p = h->ws;
     h->b.f[0] = p; p += L.f;
     h->b.f[1] = p; p += L.f;
+    // the moment state takes the place of the second population copy, 112 of its
+    // 304 bytes per node
+    if (in_moments(*prm))
+        for (int k = 0; k < 2; k++) h->b.mv[k] = (double*)((char*)h->b.f[1] + k * moment_bytes(prm));
     h->b.psi = p; p += L.psi;
     h->b.rho = L.rho ? p : nullptr; p += L.rho;
     h->b.owner[0] = (uint32_t*)p; p += L.owner;
@@ -112,7 +120,8 @@ int setup_handle(lb_handle* h, const lb_params* prm, char* ws, size_t ws_bytes, 
     h->b.bmask[0] = (uint32_t*)p; p += L.bmask;
     h->b.bmask[1] = (uint32_t*)p; p += L.bmask;
     h->b.part = (double*)p; p += L.part;
-    h->b.pfast = (double*)p; p += L.pfast;
+    h->b.pfast[0] = (double*)p; p += L.pfast;
+    h->b.pfast[1] = (double*)p; p += L.pfast;
     h->b.rec = L.rec ? (double*)p : nullptr; p += L.rec;
     h->b.kpart = (double*)p; p += L.kpart;
     h->b.red = (double*)p; p += L.red;
@@ -132,9 +141,22 @@ int setup_handle(lb_handle* h, const lb_params* prm, char* ws, size_t ws_bytes, 
     if (L.rec) chk(launch_fill_f64(h, h->b.rec, 0.0, (int64_t)(L.rec / sizeof(double))), "clear link records");
     h->kpart_len = (int64_t)(L.kpart / sizeof(double));
     chk(launch_fill_f64(h, h->b.counters, 0.0, 8), "clear counters");
-    chk(launch_fill_u32(h, (uint32_t*)h->b.health, 0u, 1), "clear health");
+    chk(launch_fill_u32(h, (uint32_t*)h->b.health, 0u, 2), "clear health");
     chk(hipStreamSynchronize(h->stream), "synchronize");
     return rc;
+}
+
+int to_moments(lb_handle* h) {
+    if (h->mom) return LB_OK;
+    LBE_HIP(h, launch_mom_from_pops(h));
+    h->mom = true;
+    return LB_OK;
+}
+int to_pops(lb_handle* h) {
+    if (!h->mom || h->pops) return LB_OK;
+    LBE_HIP(h, launch_expand(h));
+    h->pops = true;
+    return LB_OK;
 }
 
 }  // namespace lbe
@@ -142,8 +164,11 @@ int setup_handle(lb_handle* h, const lb_params* prm, char* ws, size_t ws_bytes, 
 namespace {
 
 // Staging for host transfers: the population copy that is not current (its
-// contents are dead between steps). Large enough for 5N doubles in every form.
-void* staging(lb_handle* h) { return h->b.f[1 - h->cur]; }
+// contents are dead between steps), or what the moment state leaves free of it.
+// Large enough for 5N doubles in every form.
+void* staging(lb_handle* h) {
+    return (char*)h->b.f[1 - h->cur] + (h->mom ? 2 * moment_bytes(&h->prm) : 0);
+}
 
 // Phase timing: a start / end event pair around each launch when enabled.
 hipError_t mark(lb_handle* h, int phase, bool start) {
@@ -173,11 +198,52 @@ hipError_t mark(lb_handle* h, int phase, bool start) {
         LBE_HIP(h, mark(h, ph, false));         \
     } while (0)
 
+// Owner copy `on` cleared and the moved particles drawn into it.
+int enqueue_raster(lb_handle* h) {
+    uint32_t* on = h->b.owner[1 - h->ocur];
+    LBE_HIP(h, mark(h, 5, true));
+    if (h->box.walls)
+        LBE_HIP(h, launch_clear_keep_walls(h, on, h->b.owner[h->ocur]));
+    else
+        LBE_HIP(h, launch_clear_owner(h, on));
+    LBE_HIP(h, launch_raster(h, on, 0, h->np));
+    LBE_HIP(h, mark(h, 5, false));
+    return LB_OK;
+}
+
+// One time step in moments (tau = 1): the densities of the next step come out of
+// the fluid pass itself, and nodes killed or filled by the re-rasterisation are
+// put right by kill / fill.
+int enqueue_mom_step(lb_handle* h) {
+    const int rc = to_moments(h);
+    if (rc != LB_OK) return rc;
+    if (h->np > 0) LBE_PHASE(h, 1, launch_shell(h));
+    if (h->box.walls) LBE_PHASE(h, 1, launch_wall_shell(h));
+    LBE_PHASE(h, 2, launch_mstep(h));
+    h->oprev = h->ocur;
+    h->acc_prev[0] = h->box.ax;
+    h->acc_prev[1] = h->box.ay;
+    h->acc_prev[2] = h->box.az;
+    h->pops = false;
+    if (h->np > 0) {
+        LBE_PHASE(h, 3, launch_forces(h));
+        if (h->box.pairs) LBE_PHASE(h, 3, launch_pairs(h));
+        LBE_PHASE(h, 4, launch_bodies(h));
+        const int r2 = enqueue_raster(h);
+        if (r2 != LB_OK) return r2;
+        LBE_PHASE(h, 6, launch_killfill(h));
+        h->ocur = 1 - h->ocur;
+    }
+    h->mc = 1 - h->mc;
+    return LB_OK;
+}
+
 // One time step. With particles, the densities of the next step are formed
 // right after the re-rasterisation (on nodes fluid before and after), so that
 // kill / fill reads its neighbours' densities instead of summing their
 // populations; the next step then starts from them.
 int enqueue_step(lb_handle* h) {
+    if (in_moments(h->prm)) return enqueue_mom_step(h);
     if (!h->dens_ready) LBE_PHASE(h, 0, launch_density(h, h->cur, h->ocur, -1));
     h->dens_ready = false;
     if (h->np > 0) LBE_PHASE(h, 1, launch_shell(h));
@@ -187,14 +253,8 @@ int enqueue_step(lb_handle* h) {
         LBE_PHASE(h, 3, launch_forces(h));
         if (h->box.pairs) LBE_PHASE(h, 3, launch_pairs(h));
         LBE_PHASE(h, 4, launch_bodies(h));
-        uint32_t* on = h->b.owner[1 - h->ocur];
-        LBE_HIP(h, mark(h, 5, true));
-        if (h->box.walls)
-            LBE_HIP(h, launch_clear_keep_walls(h, on, h->b.owner[h->ocur]));
-        else
-            LBE_HIP(h, launch_clear_owner(h, on));
-        LBE_HIP(h, launch_raster(h, on, 0, h->np));
-        LBE_HIP(h, mark(h, 5, false));
+        const int rc = enqueue_raster(h);
+        if (rc != LB_OK) return rc;
         LBE_PHASE(h, 0, launch_density(h, 1 - h->cur, 1 - h->ocur, h->ocur));
         LBE_PHASE(h, 6, launch_killfill(h));
         h->ocur = 1 - h->ocur;
@@ -281,6 +341,8 @@ int lb_init_fields(lb_handle* h, const double* rho_a, const double* rho_b, const
         h->box.rref[c] = h->box.rmean0[c];
         h->box.eref[c] = exp(-h->box.rref[c]);
     }
+    h->mom = false;  // the populations set here are the state
+    h->pops = true;
     double* st = (double*)staging(h);
     double* d_ra = st;
     double* d_rb = st + N;
@@ -328,7 +390,15 @@ int lb_add_ellipsoids(lb_handle* h, int32_t n, const double* radii, const double
     LBE_HIP(h, launch_fold_impulses(h));
     // plain form first: the removal below clears every solid node's slots,
     // where bounced populations of fluid neighbours may sit
-    LBE_HIP(h, launch_canonical(h));
+    // (in moments a covered node's numbers are simply not read any more)
+    const bool pops_only = !h->mom;
+    if (pops_only) LBE_HIP(h, launch_canonical(h));
+    if (h->mom && h->oprev == h->ocur) {
+        // the map of the last step is kept: a checkpoint forms its populations with it
+        LBE_HIP(h, launch_copy(h->b.owner[1 - h->ocur], h->b.owner[h->ocur],
+                               align_up((size_t)h->box.N * sizeof(uint32_t)), h->stream));
+        h->oprev = 1 - h->ocur;
+    }
     std::vector<double> t((size_t)NPFIELD * n, 0.0);
     auto F = [&](int field, int k) -> double& { return t[(size_t)field * n + k]; };
     for (int k = 0; k < n; k++) {
@@ -374,7 +444,7 @@ int lb_add_ellipsoids(lb_handle* h, int32_t n, const double* radii, const double
     h->has_solid = true;
     LBE_HIP(h, launch_pack_fast(h));
     LBE_HIP(h, launch_raster(h, h->b.owner[h->ocur], first, n));
-    LBE_HIP(h, launch_remove_covered(h));
+    if (pops_only || h->pops) LBE_HIP(h, launch_remove_covered(h));
     LBE_HIP(h, launch_stats(h));
     LBE_HIP(h, hipMemcpyAsync(after, h->b.red + kRedBlocks * 8, 7 * sizeof(double), hipMemcpyDeviceToHost, h->stream));
     LBE_HIP(h, hipMemcpyAsync(&removed, h->b.counters, sizeof(double), hipMemcpyDeviceToHost, h->stream));
@@ -417,9 +487,9 @@ int lb_read_fields(lb_handle* h, double* rho_a, double* rho_b, double* u, int32_
     LBE_NOT_BATCH(h);
     if (!h->inited) return fail(h, LB_ESTATE, "fields not initialised");
     const int64_t N = h->box.N;
-    double* st = (double*)staging(h);
     if (rho_a || rho_b || u) {
-        LBE_HIP(h, launch_fields(h, st));
+        double* st = (double*)staging(h);
+        LBE_HIP(h, launch_fields(h, rho_a ? st : nullptr, rho_b ? st + N : nullptr, u ? st + 2 * N : nullptr));
         if (rho_a) LBE_HIP(h, hipMemcpyAsync(rho_a, st, N * sizeof(double), hipMemcpyDeviceToHost, h->stream));
         if (rho_b) LBE_HIP(h, hipMemcpyAsync(rho_b, st + N, N * sizeof(double), hipMemcpyDeviceToHost, h->stream));
         if (u) LBE_HIP(h, hipMemcpyAsync(u, st + 2 * N, 3 * N * sizeof(double), hipMemcpyDeviceToHost, h->stream));
@@ -441,17 +511,8 @@ int lb_read_fields_dev(lb_handle* h, double* dev_rho_a, double* dev_rho_b, doubl
     if (!h) return LB_EINVAL;
     LBE_NOT_BATCH(h);
     if (!h->inited) return fail(h, LB_ESTATE, "fields not initialised");
-    const int64_t N = h->box.N;
-    double* st = (double*)staging(h);
-    if (dev_rho_a || dev_rho_b || dev_u) {
-        LBE_HIP(h, launch_fields(h, st));
-        if (dev_rho_a)
-            LBE_HIP(h, hipMemcpyAsync(dev_rho_a, st, N * sizeof(double), hipMemcpyDeviceToDevice, h->stream));
-        if (dev_rho_b)
-            LBE_HIP(h, hipMemcpyAsync(dev_rho_b, st + N, N * sizeof(double), hipMemcpyDeviceToDevice, h->stream));
-        if (dev_u)
-            LBE_HIP(h, hipMemcpyAsync(dev_u, st + 2 * N, 3 * N * sizeof(double), hipMemcpyDeviceToDevice, h->stream));
-    }
+    if (dev_rho_a || dev_rho_b || dev_u)
+        LBE_HIP(h, launch_fields(h, dev_rho_a, dev_rho_b, dev_u));
     if (dev_owner) LBE_HIP(h, launch_owner_codes(h, dev_owner));
     return LB_OK;
 }
@@ -608,7 +669,13 @@ int lb_save_state(lb_handle* h, void* host_buf, size_t bytes) {
     if (!h->inited) return fail(h, LB_ESTATE, "fields not initialised");
     if (bytes < lb_state_bytes(h)) return fail(h, LB_EINVAL, "buffer too small");
     LBE_HIP(h, launch_fold_impulses(h));
-    LBE_HIP(h, launch_canonical(h));  // the state is stored in plain form
+    // the state is stored in plain form
+    if (h->mom) {
+        const int rc = to_pops(h);
+        if (rc != LB_OK) return rc;
+    } else {
+        LBE_HIP(h, launch_canonical(h));
+    }
     const size_t N = (size_t)h->box.N;
     char* p = (char*)host_buf;
     double hdr[8] = {(double)h->np, h->box.rmean0[0], h->box.rmean0[1], h->box.rref[0], h->box.rref[1], h->rmax,
@@ -652,6 +719,8 @@ int lb_load_state(lb_handle* h, const void* host_buf, size_t bytes) {
             any_wall = any_wall || ow[n] == OWN_WALL;
         }
     }
+    h->mom = false;  // the populations loaded here are the state
+    h->pops = true;
     LBE_HIP(h, hipMemcpyAsync(h->b.f[h->cur], p, fb, hipMemcpyHostToDevice, h->stream));
     p += fb;
     LBE_HIP(h, hipMemcpyAsync(h->b.owner[h->ocur], p, N * sizeof(uint32_t), hipMemcpyHostToDevice, h->stream));
@@ -660,7 +729,7 @@ int lb_load_state(lb_handle* h, const void* host_buf, size_t bytes) {
     LBE_HIP(h, hipMemcpyAsync(h->b.part, p, pb, hipMemcpyHostToDevice, h->stream));
     p += pb;
     LBE_HIP(h, hipMemcpyAsync(h->b.counters, p, 8 * sizeof(double), hipMemcpyHostToDevice, h->stream));
-    LBE_HIP(h, launch_fill_u32(h, (uint32_t*)h->b.health, 0u, 1));
+    LBE_HIP(h, launch_fill_u32(h, (uint32_t*)h->b.health, 0u, 2));
     LBE_HIP(h, launch_fill_u32(h, h->b.bmask[h->cur], 0u, (int64_t)N));  // stored in plain form
     LBE_HIP(h, launch_fill_f64(h, h->b.kpart, 0.0, h->kpart_len));
     LBE_HIP(h, hipStreamSynchronize(h->stream));
