@@ -106,6 +106,18 @@ __device__ inline typename P::R empty_raw(typename P::R wref) {
     return P::dev ? -wref : typename P::R(0);
 }
 
+// c_i . u, by sums and signs only: products with the components of c_i (0, +-1)
+// would stay in the code (0 * u is not 0 for every u).
+template <class R>
+__device__ inline R dir_dot(int i, R ux, R uy, R uz) {
+    if (i == 0) return R(0);
+    const R sx = cx(i) > 0 ? ux : -ux, sy = cy(i) > 0 ? uy : -uy, sz = cz(i) > 0 ? uz : -uz;
+    if (cy(i) == 0 && cz(i) == 0) return sx;
+    if (cx(i) == 0 && cz(i) == 0) return sy;
+    if (cx(i) == 0 && cy(i) == 0) return sz;
+    return cz(i) == 0 ? sx + sy : (cy(i) == 0 ? sx + sz : sy + sz);
+}
+
 // Everything a kernel needs to know about one periodic box.
 struct Box {
     int nx, ny, nz;

@@ -34,15 +34,6 @@ __host__ __device__ constexpr int sum_dir(int k) {
     return t[k];
 }
 
-// c_i . u (i >= 1)
-__device__ inline double dir_dot(int i, double ux, double uy, double uz) {
-    const double sx = cx(i) > 0 ? ux : -ux, sy = cy(i) > 0 ? uy : -uy, sz = cz(i) > 0 ? uz : -uz;
-    if (cy(i) == 0 && cz(i) == 0) return sx;
-    if (cx(i) == 0 && cz(i) == 0) return sy;
-    if (cx(i) == 0 && cy(i) == 0) return sz;
-    return cz(i) == 0 ? sx + sy : (cy(i) == 0 ? sx + sz : sy + sz);
-}
-
 // One component of a node after the collision: a = rho (1 - 1.5 u.u) and the
 // velocity times three, so that population i is w_i (a + rho s (1 + s / 2)) with
 // s = 3 c_i . u (constants that fit an instruction).
@@ -59,7 +50,7 @@ __device__ inline double pop_eq(int i, double a, double rho, double s) {
     return wq(i) * fma_r(rho * s, fma_r(0.5, s, 1.0), a);
 }
 __device__ inline double pop_of(const Post& p, int i) {
-    return i == 0 ? pop_eq(0, p.a, p.rho, 0.0) : pop_eq(i, p.a, p.rho, dir_dot(i, p.ux, p.uy, p.uz));
+    return i == 0 ? pop_eq(0, p.a, p.rho, 0.0) : pop_eq(i, p.a, p.rho, dir_dot<double>(i, p.ux, p.uy, p.uz));
 }
 
 // Neighbour sums S = sum_i Psi(n + c_i) c_i of Eq. (3); p(i) gives Psi^A and
@@ -143,7 +134,7 @@ __device__ inline void fill_node(const Box& bx, double r0, double r1, const doub
 // C of Eq. (4) per unit density for a link along c_l into a surface moving at U.
 __device__ inline double bounce_c(int l, double Ux, double Uy, double Uz) {
 #pragma clang fp contract(off)
-    return -6.0 * wq(l) * dir_dot(l, Ux, Uy, Uz);
+    return -6.0 * wq(l) * dir_dot<double>(l, Ux, Uy, Uz);
 }
 
 // A step whose sums left a bad density somewhere raises *suspect; the nodes

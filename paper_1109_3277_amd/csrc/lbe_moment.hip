@@ -212,8 +212,8 @@ __device__ inline void mstep_body(const Box& bx, const double* __restrict__ vin,
         double(*mb)[MP] = s_m[(k + 1) & 1];  // plane k - 1
         // both components' population i from the moments at position e of plane buffer m
         auto from = [&](double(*m)[MP], int e, int i, double& v0, double& v1) {
-            v0 = pop_eq(i, m[0][e], m[1][e], i == 0 ? 0.0 : dir_dot(i, m[2][e], m[3][e], m[4][e]));
-            v1 = pop_eq(i, m[5][e], m[6][e], i == 0 ? 0.0 : dir_dot(i, m[7][e], m[8][e], m[9][e]));
+            v0 = pop_eq(i, m[0][e], m[1][e], i == 0 ? 0.0 : dir_dot<double>(i, m[2][e], m[3][e], m[4][e]));
+            v1 = pop_eq(i, m[5][e], m[6][e], i == 0 ? 0.0 : dir_dot<double>(i, m[7][e], m[8][e], m[9][e]));
         };
         // node of plane k - 1: the directions with c_iz = -1 come from plane k
         if (k > zbeg) {
@@ -363,8 +363,8 @@ __device__ inline void mstep_body(const Box& bx, const double* __restrict__ vin,
                         const int e = hit ? c : c - cy(i) * MX - cx(i);
                         double sa = 0.0, sb = 0.0;
                         if (i != 0) {
-                            sa = dir_dot(i, m[2][e], m[3][e], m[4][e]);
-                            sb = dir_dot(i, m[7][e], m[8][e], m[9][e]);
+                            sa = dir_dot<double>(i, m[2][e], m[3][e], m[4][e]);
+                            sb = dir_dot<double>(i, m[7][e], m[8][e], m[9][e]);
                             sa = hit ? -sa : sa;
                             sb = hit ? -sb : sb;
                         }
