@@ -67,9 +67,11 @@ void item_capacity(const lb_params& p, size_t cap[BI_COUNT]) {
     cap[BI_NODE_POP] = mom ? 0 : cap[BI_NODE];
     cap[BI_TILE] = cap[BI_TILE_PLAIN] = mom ? 0 : tiles;
     cap[BI_MTILE] = cap[BI_MTILE_PLAIN] = mom ? tiles : 0;
+    const size_t shares = np > 0 ? (size_t)max_shares((int)np) : 0;
     cap[BI_PART] = np;
-    cap[BI_PART_POP] = mom ? 0 : np;
-    cap[BI_PART_MOM] = mom ? np : 0;
+    cap[BI_SHARE] = shares;
+    cap[BI_SHARE_POP] = mom ? 0 : shares;
+    cap[BI_SHARE_MOM] = mom ? shares : 0;
 }
 
 struct BatchLayout {
@@ -151,6 +153,7 @@ SysDev sys_dev(const lb_handle* q) {
     d.mv[1] = q->b.mv[1];
     d.mom = q->mom ? 1 : 0;
     d.kpart = q->b.kpart;
+    d.fpart = q->b.fpart;
     d.health = q->b.health;
     d.counters = q->b.counters;
     d.cap = q->cap;
@@ -194,7 +197,10 @@ int refresh(lb_handle* h) {
         const int ncol = d.tiles_x * d.tiles_y * ((q->box.nz + B->bl.zc - 1) / B->bl.zc);
         for (int i = 0; i < nnode; i++) B->h_items[BI_NODE].push_back({s, i});
         for (int i = 0; i < q->np; i++) B->h_items[BI_PART].push_back({s, i});
-        for (int i = 0; i < q->np; i++) B->h_items[d.mom ? BI_PART_MOM : BI_PART_POP].push_back({s, i});
+        for (int i = 0; i < q->np * particle_split(q->np); i++) {
+            B->h_items[BI_SHARE].push_back({s, i});
+            B->h_items[d.mom ? BI_SHARE_MOM : BI_SHARE_POP].push_back({s, i});
+        }
         if (d.mom) {
             for (int i = 0; i < ncol; i++) B->h_items[q->has_solid ? BI_MTILE : BI_MTILE_PLAIN].push_back({s, i});
         } else {

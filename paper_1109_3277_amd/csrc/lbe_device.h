@@ -291,9 +291,24 @@ struct Tiles {
     bool zrun = false;  // tile kernel: walk z before y (see fused_body)
 };
 
-// Per-particle kernels run one block of kPB threads per particle, looping
-// over the nodes of the particle's box in chunks of kPB nodes.
+// Per-particle kernels loop over the nodes of a particle's box with blocks of kPB
+// threads: one block per particle where there are many, several where there
+// are few, so that a handful of particles still spreads over the chip (a single
+// block walks the 64^3 adsorption box's ellipsoid of 25^3 nodes in 61 rounds of
+// memory latency). The number follows from the system's own particle count, so
+// that the sums over the blocks' shares run alike in a batch and alone. It is
+// at most 16, and about 1024 blocks in all.
 constexpr int kPB = 256;
+constexpr int kMaxSplit = 16;
+__host__ __device__ inline int particle_split(int np) {
+    const int s = np > 0 ? 1024 / np : 1;
+    return s < 1 ? 1 : (s > kMaxSplit ? kMaxSplit : s);
+}
+// Shares of all particles of a system, at most, for a capacity of cap.
+__host__ __device__ inline int max_shares(int cap) {
+    const int a = cap * kMaxSplit, b = cap > 1024 ? cap : 1024;
+    return a < b ? a : b;
+}
 
 // Link records of a particle: one record of kRec doubles per node of its
 // record box (its bounding box grown by one node on every side, each edge at
@@ -406,6 +421,7 @@ struct SysDev {
     double* rec;
     double* pfast[2];
     double* kpart;
+    double* fpart;
     int* health;
     double* counters;  // [0] fluid mass removed at particle placement
     int cap, np;

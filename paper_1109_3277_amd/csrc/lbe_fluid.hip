@@ -1079,10 +1079,9 @@ __global__ __launch_bounds__(256) void k_wall_shell_batch(const SysDev* __restri
     if (d.box.walls == 0) return;
     const int64_t n = (int64_t)w.local * 256 + threadIdx.x;
     if (n >= d.box.N) return;
-    if (d.mom)
-        wall_shell_node<double>(d.box, d.mv[o] + 5 * d.box.N, d.mv[o], d.owner[o], n);
-    else
-        wall_shell_node<R>(d.box, (R*)d.psi, (const R*)sys_rho(d), d.owner[o], n);
+    R* psi = d.mom ? (R*)(d.mv[o] + 5 * d.box.N) : (R*)d.psi;  // (moments: R is double)
+    const R* rho = d.mom ? (const R*)d.mv[o] : (const R*)sys_rho(d);
+    wall_shell_node<R>(d.box, psi, rho, d.owner[o], n);
 }
 // Owner copy cleared for re-rasterisation, wall nodes kept (from the current copy).
 __global__ void k_clear_keep_walls(uint32_t* __restrict__ dst, const uint32_t* __restrict__ cur, int64_t n) {

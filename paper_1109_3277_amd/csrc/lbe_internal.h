@@ -23,7 +23,8 @@ struct Buffers {
     double* rec = nullptr;             // link records, cap x kext^3 cells x kRec
     double* mv[2] = {nullptr, nullptr};  // tau = 1, FP64: the two copies of the moment state (lbe_moment.h), in f[1]
     double* pfast[2] = {nullptr, nullptr};  // packed particle copies of owner copy 0 / 1, cap x kPF
-    double* kpart = nullptr;           // kill/fill impulse and masses of the last step, cap x 8
+    double* kpart = nullptr;           // kill/fill impulse and masses of the last step, 8 per particle and share
+    double* fpart = nullptr;           // link force and torque of the step, 8 (6 used) per particle and share
     double* red = nullptr;             // reduction partials, kRedBlocks x 8, then totals
     double* counters = nullptr;        // [0] fluid mass removed at particle placement (cumulative)
     int* health = nullptr;             // [0] nonzero once a NaN / negative density was seen, [1] a step's suspicion
@@ -45,9 +46,11 @@ struct BatchState;
 // BI_TILE: tiles of systems with particles; BI_TILE_PLAIN: tiles of systems
 // without (they run the kernel a lone handle would run).
 // FP64 systems with tau = 1 advance in moments (lbe_moment.h) and have their own
-// lists; BI_NODE and BI_PART cover every system.
+// lists; BI_NODE, BI_PART (particles) and BI_SHARE (particles by shares, see
+// particle_split) cover every system.
 enum BatchItems {
-    BI_NODE = 0, BI_NODE_POP, BI_TILE, BI_TILE_PLAIN, BI_MTILE, BI_MTILE_PLAIN, BI_PART, BI_PART_POP, BI_PART_MOM,
+    BI_NODE = 0, BI_NODE_POP, BI_TILE, BI_TILE_PLAIN, BI_MTILE, BI_MTILE_PLAIN, BI_PART, BI_SHARE, BI_SHARE_POP,
+    BI_SHARE_MOM,
     BI_COUNT
 };
 struct BatchLaunch {
@@ -110,7 +113,7 @@ namespace lbe {
 constexpr size_t kAlign = 256;
 inline size_t align_up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
 struct Layout {
-    size_t f, psi, rho, owner, bmask, part, pfast, rec, kpart, red, counters, health, cells, total;
+    size_t f, psi, rho, owner, bmask, part, pfast, rec, kpart, fpart, red, counters, health, cells, total;
 };
 bool params_ok(const lb_params* p, std::string* why);
 Layout layout_of(const lb_params* p);

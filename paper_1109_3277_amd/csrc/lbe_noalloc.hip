@@ -114,7 +114,7 @@ __global__ __launch_bounds__(256) void k_stats_nb_one(SysDev d, int c, int m, in
 
 // Totals of system s in the order lb_stats forms them: partials in block
 // order; mass removed = placement removal + sum over particles, in index order,
-// of (killed + last step's killed) - (filled + last step's filled).
+// of (killed + last step's killed, share by share) - (filled + last step's filled).
 __device__ void stats_final(const SysDev& d, const double* __restrict__ sc, double* __restrict__ out) {
     double t[7] = {0, 0, 0, 0, 0, 0, 0};
     for (int b = 0; b < kNB; b++) {
@@ -122,9 +122,15 @@ __device__ void stats_final(const SysDev& d, const double* __restrict__ sc, doub
         t[6] = fmax(t[6], sc[(size_t)b * 8 + 6]);
     }
     double removed = d.counters[0];
-    for (int p = 0; p < d.np; p++)
-        removed += (d.part[KMASS * d.cap + p] + d.kpart[(size_t)8 * p + 6]) -
-                   (d.part[FMASS * d.cap + p] + d.kpart[(size_t)8 * p + 7]);
+    const int sp = particle_split(d.np);
+    for (int p = 0; p < d.np; p++) {
+        double km = d.part[KMASS * d.cap + p], fm = d.part[FMASS * d.cap + p];
+        for (int s = 0; s < sp; s++) {
+            km += d.kpart[8 * ((size_t)p * sp + s) + 6];
+            fm += d.kpart[8 * ((size_t)p * sp + s) + 7];
+        }
+        removed += km - fm;
+    }
     out[0] = t[0];
     out[1] = t[1];
     out[2] = t[2];

@@ -2,8 +2,8 @@
 // torque of each particle, rigid-body update, rasterisation of the ellipsoids onto
 // the owner map, and kill / fill of nodes that change side.
 //
-// The per-node particle kernels run one block per particle that loops over the
-// nodes of the particle's box (several nodes' loads in flight per thread).
+// The per-node particle kernels loop over the nodes of a particle's box with one
+// block, or with a few that share it (several nodes' loads in flight per thread).
 // Forces, torques and kill/fill impulses are summed in fixed orders (per-block
 // partial slots, added in slot order): particle state is reproducible bit for
 // bit.
@@ -103,9 +103,10 @@ __device__ inline int64_t node_index(const Box& bx, int x, int y, int z) {
 
 // ---------------------------------------------------------------- raster
 // Rasterise particle p into owner with atomicMin (the smallest index owns a
-// node covered by several particles): one block loops over p's ellipsoid box.
+// node covered by several particles): share sh of nsh loops over its part of p's
+// ellipsoid box.
 __device__ inline void raster_body(const Box& bx, const double* __restrict__ part, int cap,
-                                   uint32_t* __restrict__ owner, int p) {
+                                   uint32_t* __restrict__ owner, int p, int sh, int nsh) {
     int lo[3], sz[3];
     if (!ellipsoid_box(bx, part, cap, p, lo, sz)) return;  // invalid state: touch nothing
     const double X[3] = {part[PX * cap + p], part[PY * cap + p], part[PZ * cap + p]};
@@ -115,8 +116,9 @@ __device__ inline void raster_body(const Box& bx, const double* __restrict__ par
     const double ia2 = 1.0 / (rperp * rperp), ic2 = 1.0 / (rpar * rpar);
     const int total = sz[0] * sz[1] * sz[2];
     const int Ls[3] = {bx.nx, bx.ny, bx.nz};
-    BoxWalk w(lo, sz, Ls, threadIdx.x, kPB);
-    for (int t = threadIdx.x; t < total; t += kPB, w.next()) {
+    const int t0 = sh * kPB + (int)threadIdx.x, step = nsh * kPB;
+    BoxWalk w(lo, sz, Ls, t0, step);
+    for (int t = t0; t < total; t += step, w.next()) {
         const int x = w.x(), y = w.y(), z = w.z();
         const double dx = minimg((double)x - X[0], bx.nx);
         const double dy = minimg((double)y - X[1], bx.ny);
@@ -133,15 +135,16 @@ __device__ inline void raster_body(const Box& bx, const double* __restrict__ par
     }
 }
 __global__ __launch_bounds__(kPB) void k_raster(Box bx, const double* __restrict__ part, int cap,
-                                                uint32_t* __restrict__ owner, int first) {
-    raster_body(bx, part, cap, owner, first + blockIdx.x);
+                                                uint32_t* __restrict__ owner, int first, int nsh) {
+    raster_body(bx, part, cap, owner, first + blockIdx.x / nsh, blockIdx.x % nsh, nsh);
 }
-// Batched: item = (system, particle), into the owner copy `o` of every system.
+// Batched: item = (system, share), into the owner copy `o` of every system.
 __global__ __launch_bounds__(kPB) void k_raster_batch(const SysDev* __restrict__ sd,
                                                       const WorkItem* __restrict__ items, int o) {
     const WorkItem w = items[blockIdx.x];
     const SysDev& d = sd[w.sys];
-    raster_body(d.box, d.part, d.cap, d.owner[o], w.local);
+    const int nsh = particle_split(d.np);
+    raster_body(d.box, d.part, d.cap, d.owner[o], w.local / nsh, w.local % nsh, nsh);
 }
 
 // ---------------------------------------------------------------- S2
@@ -149,17 +152,18 @@ __global__ __launch_bounds__(kPB) void k_raster_batch(const SysDev* __restrict__
 // takes their mean density; the particle colour is added to A if positive,
 // its magnitude to B if negative. Densities are recovered from the stored
 // Psi and the result is stored as Psi.
-// One block per particle; only nodes of p change. The block takes p's box in
-// segments of kShellSeg nodes: it loads the owner codes of a whole segment
-// (kShellPT per thread, all in flight), lists p's nodes in LDS, then gives
-// each listed node to one thread for its 18 neighbour gathers. A node's
-// result depends on its neighbours only, so the list order does not matter.
-constexpr int kShellPT = 20;
-constexpr int kShellSeg = kShellPT * kPB;
-template <class R>
+// Only nodes of p change. Share sh of nsh takes its segments of PT * kPB nodes of
+// p's box: it loads the owner codes of a whole segment (PT per thread, all in
+// flight), lists p's nodes in LDS, then gives each listed node to one thread for
+// its 18 neighbour gathers. A node's result depends on its neighbours only, so the
+// list order does not matter. Whole particles take long segments, shares of
+// them short ones, one or two each.
+constexpr int kShellLong = 20, kShellShort = 4;
+template <class R, int PT>
 __device__ inline void shell_body(const Box& bx, R* __restrict__ psi, const R* __restrict__ rho,
                                   const uint32_t* __restrict__ owner, const double* __restrict__ part, int cap,
-                                  int p) {
+                                  int p, int sh, int nsh) {
+    constexpr int kSeg = PT * kPB;
     const int nx = bx.nx, ny = bx.ny, nz = bx.nz;
     const int64_t N = bx.N;
     int lo[3] = {0, 0, 0}, sz[3] = {0, 0, 0};
@@ -168,22 +172,22 @@ __device__ inline void shell_body(const Box& bx, R* __restrict__ psi, const R* _
     const R* dens = bx.psi_kind == 0 ? psi : rho;
     const double dr = part[DRHO * cap + p];
     const int Ls[3] = {nx, ny, nz};
-    __shared__ uint32_t s_list[kShellSeg];
+    __shared__ uint32_t s_list[kSeg];
     __shared__ int s_cnt;
-    for (int base = 0; base < total; base += kShellSeg) {
+    for (int base = sh * kSeg; base < total; base += nsh * kSeg) {
         if (threadIdx.x == 0) s_cnt = 0;
         __syncthreads();
         {
             BoxWalk w(lo, sz, Ls, base + (int)threadIdx.x, kPB);
-            uint32_t ow[kShellPT];
+            uint32_t ow[PT];
 #pragma unroll
-            for (int k = 0; k < kShellPT; k++) {
+            for (int k = 0; k < PT; k++) {
                 ow[k] = OWN_FLUID;
                 if (base + (int)threadIdx.x + k * kPB < total) ow[k] = owner[node_index(bx, w.x(), w.y(), w.z())];
                 w.next();
             }
 #pragma unroll
-            for (int k = 0; k < kShellPT; k++)
+            for (int k = 0; k < PT; k++)
                 if (ow[k] == (uint32_t)p) s_list[atomicAdd(&s_cnt, 1)] = (uint32_t)(base + (int)threadIdx.x + k * kPB);
         }
         __syncthreads();
@@ -233,32 +237,33 @@ __device__ inline void shell_body(const Box& bx, R* __restrict__ psi, const R* _
         __syncthreads();  // the list is read before the next segment resets it
     }
 }
-template <class R>
+template <class R, int PT>
 __global__ __launch_bounds__(kPB) void k_shell(Box bx, R* __restrict__ psi, const R* __restrict__ rho,
                                                const uint32_t* __restrict__ owner, const double* __restrict__ part,
-                                               int cap, int* __restrict__ suspect) {
+                                               int cap, int* __restrict__ suspect, int nsh) {
     if (blockIdx.x == 0 && threadIdx.x == 0) *suspect = 0;  // of the step that begins
-    shell_body<R>(bx, psi, rho, owner, part, cap, blockIdx.x);
+    shell_body<R, PT>(bx, psi, rho, owner, part, cap, blockIdx.x / nsh, blockIdx.x % nsh, nsh);
 }
 template <class R>
 __global__ __launch_bounds__(kPB) void k_shell_batch(const SysDev* __restrict__ sd, const WorkItem* __restrict__ items,
                                                      int o) {
     const WorkItem w = items[blockIdx.x];
     const SysDev& d = sd[w.sys];
-    if (d.mom)
-        shell_body<double>(d.box, d.mv[o] + 5 * d.box.N, d.mv[o], d.owner[o], d.part, d.cap, w.local);
-    else
-        shell_body<R>(d.box, (R*)d.psi, (const R*)d.rho, d.owner[o], d.part, d.cap, w.local);
+    const int nsh = particle_split(d.np), p = w.local / nsh, sh = w.local % nsh;
+    R* psi = d.mom ? (R*)(d.mv[o] + 5 * d.box.N) : (R*)d.psi;  // (moments: R is double)
+    const R* rho = d.mom ? (const R*)d.mv[o] : (const R*)d.rho;
+    shell_body<R, kShellShort>(d.box, psi, rho, d.owner[o], d.part, d.cap, p, sh, nsh);
 }
 
 // ---------------------------------------------------------------- S6 forces
 // Bounce-back force and torque of particle p (Eq. (5)). The fused kernel left,
 // for every fluid node n linked to p, the node's force F_n = sum over its
 // links into p of (2 f*_i + C) c_i (both components) in p's record cell of n.
-// The force is the sum of the F_n and the torque the sum of r_n x F_n. One
-// block per particle walks the record cells that can hold a link: cell t of
-// the walk goes to thread t mod kPB, each thread's cells in increasing order,
-// then a fixed block sum, so the result is reproducible bit for bit. Records
+// The force is the sum of the F_n and the torque the sum of r_n x F_n. The blocks
+// of p's shares walk the record cells that can hold a link, in chunks of U * kPB
+// cells: each thread's cells in increasing order, then a fixed block sum into
+// the share's slot of fpart, which the body update adds in order, so the result is
+// reproducible bit for bit. Records
 // read are cleared for the next step. A linked fluid node lies within sqrt(2)
 // of a node of p. In coordinates scaled by the semi-axes that is a step of at
 // most sqrt(2) / min(R_par, R_perp), so the node lies inside p's ellipsoid
@@ -267,7 +272,8 @@ __global__ __launch_bounds__(kPB) void k_shell_batch(const SysDev* __restrict__ 
 // record box spans the whole lattice, all of them), and loads only the cells
 // inside the scaled ellipsoid itself; other cells are never written.
 __device__ inline void linkforce_body(const Box& bx, double* __restrict__ rec, int rstride,
-                                      double* __restrict__ part, int cap, int p) {
+                                      double* __restrict__ part, int cap, double* __restrict__ fpart, int p, int sh,
+                                      int nsh) {
     const int Ls[3] = {bx.nx, bx.ny, bx.nz};
     const double X[3] = {part[PX * cap + p], part[PY * cap + p], part[PZ * cap + p]};
     int lo[3] = {0, 0, 0}, sz[3] = {0, 0, 0}, esz[3];
@@ -303,13 +309,14 @@ __device__ inline void linkforce_body(const Box& bx, double* __restrict__ rec, i
     double* rp = rec + (size_t)p * rstride * kRec;
     double acc[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
     constexpr int U = 4;  // cells per thread in flight
-    BoxWalk w(slo, ssz, Ls, threadIdx.x, kPB);
-    for (int base = 0; base < cells; base += U * kPB) {
+    // (the walker moves by the blocks' chunks: U rows of kPB cells in turn from each)
+    BoxWalk w(slo, ssz, Ls, sh * kPB + (int)threadIdx.x, nsh * kPB);
+    for (int base = 0; base < cells; base += U * nsh * kPB) {
         double F[U][3], r[U][3];
         int cell[U];
 #pragma unroll
         for (int k = 0; k < U; k++, w.next()) {
-            const int t = base + k * kPB + (int)threadIdx.x;
+            const int t = base + (k * nsh + sh) * kPB + (int)threadIdx.x;
             F[k][0] = F[k][1] = F[k][2] = 0.0;
             r[k][0] = r[k][1] = r[k][2] = 0.0;
             cell[k] = ((off[2] + w.iz) * esz[1] + off[1] + w.iy) * esz[0] + off[0] + w.ix;
@@ -343,21 +350,21 @@ __device__ inline void linkforce_body(const Box& bx, double* __restrict__ rec, i
     }
     double tot[6];
     block_sum<6>(acc, tot);
-    if (threadIdx.x == 0) {
-        const int fld[6] = {FX, FY, FZ, TX, TY, TZ};
-        for (int k = 0; k < 6; k++) part[fld[k] * cap + p] = tot[k];
-    }
+    if (threadIdx.x == 0)
+        for (int k = 0; k < 6; k++) fpart[((size_t)p * nsh + sh) * 8 + k] = tot[k];
 }
 __global__ __launch_bounds__(kPB, 4) void k_linkforce(Box bx, double* __restrict__ rec, int rstride,
-                                                   double* __restrict__ part, int cap) {
-    linkforce_body(bx, rec, rstride, part, cap, blockIdx.x);
+                                                   double* __restrict__ part, int cap, double* __restrict__ fpart,
+                                                   int nsh) {
+    linkforce_body(bx, rec, rstride, part, cap, fpart, blockIdx.x / nsh, blockIdx.x % nsh, nsh);
 }
-// Batched: item = (system, particle).
+// Batched: item = (system, share).
 __global__ __launch_bounds__(kPB, 4) void k_linkforce_batch(const SysDev* __restrict__ sd,
                                                          const WorkItem* __restrict__ items) {
     const WorkItem w = items[blockIdx.x];
     const SysDev& d = sd[w.sys];
-    linkforce_body(d.box, d.rec, d.kext * d.kext * d.kext, d.part, d.cap, w.local);
+    const int nsh = particle_split(d.np);
+    linkforce_body(d.box, d.rec, d.kext * d.kext * d.kext, d.part, d.cap, d.fpart, w.local / nsh, w.local % nsh, nsh);
 }
 
 // ---------------------------------------------------------------- S7
@@ -365,25 +372,35 @@ __global__ __launch_bounds__(kPB, 4) void k_linkforce_batch(const SysDev* __rest
 // T_pairs (the pair terms are zero unless particle-particle interactions are
 // on); V += F/M,
 // X = wrap(X + V); L += T; W = R I^-1 R^T L with the old orientation;
-// q <- normalise(exp(W/2) (x) q). F_links / T_links come from k_linkforce;
-// J / H are the stored impulses plus the kill/fill slots. One wave per
-// particle: lane l sums slots l, l + 64, ... in order, then a fixed shuffle
-// tree; lane 0 updates the body.
+// q <- normalise(exp(W/2) (x) q). F_links / T_links come from k_linkforce's slots;
+// J / H are the stored impulses plus the kill/fill slots. One wave per particle:
+// lane l < 8 sums slot number l of the kill/fill shares in order, lane 8 + l those
+// of the link forces; lane 0 updates the body.
 __device__ inline void bodies_body(const Box& bx, double* __restrict__ part, int cap,
-                                   const double* __restrict__ kpart, int nk, double* __restrict__ pfast, int p) {
+                                   const double* __restrict__ kpart, const double* __restrict__ fpart, int nk,
+                                   double* __restrict__ pfast, int p) {
     const int lane = threadIdx.x;
-    double Jk[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-    for (int s = lane; s < nk; s += 64)
-        for (int k = 0; k < 8; k++) Jk[k] += kpart[((size_t)p * nk + s) * 8 + k];
+    double mine = 0.0;
+    if (lane < 14) {
+        const double* src = (lane < 8 ? kpart + lane : fpart + (lane - 8)) + (size_t)p * nk * 8;
+        for (int s = 0; s < nk; s += 4) {  // four loads in flight, added in order
+            double v[4];
 #pragma unroll
-    for (int k = 0; k < 8; k++)
-        for (int off = 32; off > 0; off >>= 1) Jk[k] += __shfl_down(Jk[k], off, 64);
+            for (int j = 0; j < 4; j++) v[j] = s + j < nk ? src[8 * (s + j)] : 0.0;
+#pragma unroll
+            for (int j = 0; j < 4; j++) mine += v[j];
+        }
+    }
+    double Jk[8], Fl[6];
+#pragma unroll
+    for (int k = 0; k < 8; k++) Jk[k] = __shfl(mine, k, 64);
+#pragma unroll
+    for (int k = 0; k < 6; k++) Fl[k] = __shfl(mine, 8 + k, 64);
     if (lane != 0) return;
     double* P = part;
 #define F_(k) P[(k) * cap + p]
     F_(KMASS) += Jk[6];
     F_(FMASS) += Jk[7];
-    const double Fl[6] = {F_(FX), F_(FY), F_(FZ), F_(TX), F_(TY), F_(TZ)};
     const double J[3] = {F_(JX) + Jk[0], F_(JY) + Jk[1], F_(JZ) + Jk[2]};
     const double H[3] = {F_(HX) + Jk[3], F_(HY) + Jk[4], F_(HZ) + Jk[5]};
     double F[3], T[3];
@@ -464,15 +481,15 @@ __device__ inline void bodies_body(const Box& bx, double* __restrict__ part, int
     pack_fast(bx, part, cap, p, pfast);
 }
 __global__ __launch_bounds__(64) void k_bodies(Box bx, double* __restrict__ part, int cap,
-                                               const double* __restrict__ kpart, int nk,
-                                               double* __restrict__ pfast) {
-    bodies_body(bx, part, cap, kpart, nk, pfast, blockIdx.x);
+                                               const double* __restrict__ kpart, const double* __restrict__ fpart,
+                                               int nk, double* __restrict__ pfast) {
+    bodies_body(bx, part, cap, kpart, fpart, nk, pfast, blockIdx.x);
 }
 __global__ __launch_bounds__(64) void k_bodies_batch(const SysDev* __restrict__ sd,
                                                      const WorkItem* __restrict__ items, int o) {
     const WorkItem w = items[blockIdx.x];
     const SysDev& d = sd[w.sys];
-    bodies_body(d.box, d.part, d.cap, d.kpart, 1, d.pfast[1 - o], w.local);
+    bodies_body(d.box, d.part, d.cap, d.kpart, d.fpart, particle_split(d.np), d.pfast[1 - o], w.local);
 }
 
 // Packed particle table of particles [0, np) from the particle table.
@@ -517,9 +534,9 @@ __device__ inline R feq_p(int i, R rho, R ux, R uy, R uz) {
 //                      f = f^eq(rho_new^c, u), J_p -= sum_c rho_new^c u, H_p -= r x that;
 //                      the node's Psi (and rho) follow from the stored f.
 // Each changing node is handled by exactly one thread (of its owner's block).
-// One block loops over that box, eight nodes per thread in flight; the
-// block's fixed-order sum is the particle's impulse (and killed / filled
-// mass) of this step. A box wider than kext (a move of more than two
+// The blocks of p's shares loop over that box, eight nodes per thread in flight;
+// each block's fixed-order sum is its share of the particle's impulse (and killed
+// / filled mass) of this step. A box wider than kext (a move of more than two
 // spacings) raises health bit 2.
 template <class P>
 __device__ inline void killfill_node(const Box& bx, typename P::S* __restrict__ f,
@@ -705,7 +722,8 @@ __device__ inline void killfill_mom_node(const Box& bx, double* __restrict__ v, 
 template <class Node>
 __device__ inline void killfill_body(const Box& bx, const uint32_t* __restrict__ own_old,
                                      const uint32_t* __restrict__ own_new, const double* __restrict__ part, int cap,
-                                     int kext, double* __restrict__ kpart, int* __restrict__ health, int p, Node node) {
+                                     int kext, double* __restrict__ kpart, int* __restrict__ health, int p, int sh,
+                                     int nsh, Node node) {
     const int Ls[3] = {bx.nx, bx.ny, bx.nz};
     double acc[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};  // J, H, killed mass, filled mass
     int lo[3] = {0, 0, 0}, sz[3] = {0, 0, 0};
@@ -736,11 +754,11 @@ __device__ inline void killfill_body(const Box& bx, const uint32_t* __restrict__
     }
     const int total = ok ? sz[0] * sz[1] * sz[2] : 0;
     constexpr int U = 8;  // nodes per thread with owner loads in flight (4: +6 %, 12: +3 % time)
-    for (int base = 0; base < total; base += U * kPB) {
+    for (int base = sh * kPB; base < total; base += U * nsh * kPB) {
         uint32_t oo[U], on[U];  // every owner load of this thread issued before any is used
 #pragma unroll
         for (int k = 0; k < U; k++) {
-            const int t = base + k * kPB + threadIdx.x;
+            const int t = base + k * nsh * kPB + (int)threadIdx.x;
             oo[k] = on[k] = OWN_FLUID;
             if (t < total) {
                 int ix, iy, iz;
@@ -764,7 +782,7 @@ __device__ inline void killfill_body(const Box& bx, const uint32_t* __restrict__
             const uint32_t b = (todo >> (2 * k)) & 3u;
             if (b == 0u) continue;
             int ix, iy, iz;
-            box_node(base + k * kPB + threadIdx.x, sz, ix, iy, iz);
+            box_node(base + k * nsh * kPB + (int)threadIdx.x, sz, ix, iy, iz);
             const int x = wrapc_any(lo[0] + ix, Ls[0]), y = wrapc_any(lo[1] + iy, Ls[1]),
                       z = wrapc_any(lo[2] + iz, Ls[2]);
             node(b == 1u, x, y, z, node_index(bx, x, y, z), Xn, acc);
@@ -773,7 +791,7 @@ __device__ inline void killfill_body(const Box& bx, const uint32_t* __restrict__
     double tot[8];
     block_sum<8>(acc, tot);
     if (threadIdx.x == 0)
-        for (int k = 0; k < 8; k++) kpart[(size_t)p * 8 + k] = tot[k];
+        for (int k = 0; k < 8; k++) kpart[((size_t)p * nsh + sh) * 8 + k] = tot[k];
 }
 template <class P>
 __global__ __launch_bounds__(kPB, 3) void k_killfill(Box bx, typename P::S* __restrict__ f,
@@ -781,23 +799,24 @@ __global__ __launch_bounds__(kPB, 3) void k_killfill(Box bx, typename P::S* __re
                                                   const uint32_t* __restrict__ own_new, uint32_t* __restrict__ bmask,
                                                   typename P::R* __restrict__ psi, typename P::R* __restrict__ rho,
                                                   const double* __restrict__ part, int cap, int kext,
-                                                  double* __restrict__ kpart, int* __restrict__ health) {
-    const int p = blockIdx.x;
-    killfill_body(bx, own_old, own_new, part, cap, kext, kpart, health, p,
+                                                  double* __restrict__ kpart, int* __restrict__ health, int nsh) {
+    const int p = blockIdx.x / nsh;
+    killfill_body(bx, own_old, own_new, part, cap, kext, kpart, health, p, blockIdx.x % nsh, nsh,
                   [&](bool kill, int x, int y, int z, int64_t n, const double(&Xn)[3], double(&acc)[8]) {
                       killfill_node<P>(bx, f, own_old, own_new, bmask, psi, rho, part, cap, p, kill, x, y, z, n, Xn,
                                        acc);
                   });
 }
-// Batched: item = (system, particle); owner copy `oo` is the old map, 1 - oo
+// Batched: item = (system, share); owner copy `oo` is the old map, 1 - oo
 // the new one; populations copy `fd`.
 template <class P>
 __global__ __launch_bounds__(kPB, 3) void k_killfill_batch(const SysDev* __restrict__ sd,
                                                         const WorkItem* __restrict__ items, int oo, int fd) {
     const WorkItem w = items[blockIdx.x];
     const SysDev& d = sd[w.sys];
-    const int p = w.local;
-    killfill_body(d.box, d.owner[oo], d.owner[1 - oo], d.part, d.cap, d.kext, d.kpart, d.health, p,
+    const int nsh = particle_split(d.np), p = w.local / nsh;
+    killfill_body(d.box, d.owner[oo], d.owner[1 - oo], d.part, d.cap, d.kext, d.kpart, d.health, p, w.local % nsh,
+                  nsh,
                   [&](bool kill, int x, int y, int z, int64_t n, const double(&Xn)[3], double(&acc)[8]) {
                       killfill_node<P>(d.box, (typename P::S*)d.f[fd], d.owner[oo], d.owner[1 - oo], d.bmask[fd],
                                        (typename P::R*)d.psi, (typename P::R*)d.rho, d.part, d.cap, p, kill, x, y, z, n,
@@ -809,11 +828,12 @@ __global__ __launch_bounds__(kPB, 3) void k_killfill_mom(Box bx, double* __restr
                                                          const uint32_t* __restrict__ own_old,
                                                          const uint32_t* __restrict__ own_new,
                                                          const double* __restrict__ part, int cap, int kext,
-                                                         double* __restrict__ kpart, int* __restrict__ health) {
-    const int p = blockIdx.x;
+                                                         double* __restrict__ kpart, int* __restrict__ health,
+                                                         int nsh) {
+    const int p = blockIdx.x / nsh;
     // (filled nodes are not fluid in own_old: the check and the fills do not meet)
-    check_suspect(bx, v, own_old, own_new, health + 1, health, p, gridDim.x);
-    killfill_body(bx, own_old, own_new, part, cap, kext, kpart, health, p,
+    check_suspect(bx, v, own_old, own_new, health + 1, health, blockIdx.x, gridDim.x);
+    killfill_body(bx, own_old, own_new, part, cap, kext, kpart, health, p, blockIdx.x % nsh, nsh,
                   [&](bool kill, int x, int y, int z, int64_t n, const double(&Xn)[3], double(&acc)[8]) {
                       killfill_mom_node(bx, v, v0, own_old, own_new, part, cap, p, kill, x, y, z, n, Xn, acc);
                   });
@@ -822,8 +842,9 @@ __global__ __launch_bounds__(kPB, 3) void k_killfill_mom_batch(const SysDev* __r
                                                                const WorkItem* __restrict__ items, int c) {
     const WorkItem w = items[blockIdx.x];
     const SysDev& d = sd[w.sys];
-    const int p = w.local;
-    killfill_body(d.box, d.owner[c], d.owner[1 - c], d.part, d.cap, d.kext, d.kpart, d.health, p,
+    const int nsh = particle_split(d.np), p = w.local / nsh;
+    killfill_body(d.box, d.owner[c], d.owner[1 - c], d.part, d.cap, d.kext, d.kpart, d.health, p, w.local % nsh,
+                  nsh,
                   [&](bool kill, int x, int y, int z, int64_t n, const double(&Xn)[3], double(&acc)[8]) {
                       killfill_mom_node(d.box, d.mv[1 - c], d.mv[c], d.owner[c], d.owner[1 - c], d.part, d.cap, p, kill,
                                         x, y, z, n, Xn, acc);
@@ -845,30 +866,33 @@ int killfill_extent(int nx, int ny, int nz, double rb) {
 }
 int kill_ext(const lb_handle* h) { return killfill_extent(h->box.nx, h->box.ny, h->box.nz, h->rmax); }
 
+template <class R, int PT>
+static void launch_shell_t(lb_handle* h, int nsh) {
+    hipLaunchKernelGGL((k_shell<R, PT>), dim3(h->np * nsh), dim3(kPB), 0, h->stream, h->box, (R*)psi_now(h),
+                       (const R*)(h->mom ? rho_now(h) : h->b.rho), h->b.owner[h->ocur], h->b.part, h->cap,
+                       h->b.health + 1, nsh);
+}
 hipError_t launch_shell(lb_handle* h) {
     if (h->np <= 0) return hipSuccess;
+    const int nsh = particle_split(h->np);
     if (h->prm.precision == LB_FP64)
-        hipLaunchKernelGGL(k_shell<double>, dim3(h->np), dim3(kPB), 0, h->stream, h->box, (double*)psi_now(h),
-                           (const double*)(h->mom ? rho_now(h) : h->b.rho), h->b.owner[h->ocur], h->b.part, h->cap,
-                           h->b.health + 1);
+        nsh == 1 ? launch_shell_t<double, kShellLong>(h, nsh) : launch_shell_t<double, kShellShort>(h, nsh);
     else
-        hipLaunchKernelGGL(k_shell<float>, dim3(h->np), dim3(kPB), 0, h->stream, h->box, (float*)psi_now(h),
-                           (const float*)(h->mom ? rho_now(h) : h->b.rho), h->b.owner[h->ocur], h->b.part, h->cap,
-                           h->b.health + 1);
+        nsh == 1 ? launch_shell_t<float, kShellLong>(h, nsh) : launch_shell_t<float, kShellShort>(h, nsh);
     return hipGetLastError();
 }
 
 hipError_t launch_forces(lb_handle* h) {
     if (h->np <= 0) return hipSuccess;
-    const int ke = kill_ext(h);
-    hipLaunchKernelGGL(k_linkforce, dim3(h->np), dim3(kPB), 0, h->stream, h->box, h->b.rec, ke * ke * ke, h->b.part,
-                       h->cap);
+    const int ke = kill_ext(h), nsh = particle_split(h->np);
+    hipLaunchKernelGGL(k_linkforce, dim3(h->np * nsh), dim3(kPB), 0, h->stream, h->box, h->b.rec, ke * ke * ke,
+                       h->b.part, h->cap, h->b.fpart, nsh);
     return hipGetLastError();
 }
 hipError_t launch_bodies(lb_handle* h) {
     if (h->np <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_bodies, dim3(h->np), dim3(64), 0, h->stream, h->box, h->b.part, h->cap, h->b.kpart, 1,
-                       h->b.pfast[1 - h->ocur]);  // belongs to the owner map about to be drawn
+    hipLaunchKernelGGL(k_bodies, dim3(h->np), dim3(64), 0, h->stream, h->box, h->b.part, h->cap, h->b.kpart,
+                       h->b.fpart, particle_split(h->np), h->b.pfast[1 - h->ocur]);  // belongs to the owner map about to be drawn
     return hipGetLastError();
 }
 hipError_t launch_pack_fast(lb_handle* h) {
@@ -881,7 +905,7 @@ hipError_t launch_pack_fast(lb_handle* h) {
 hipError_t launch_fold_impulses(lb_handle* h) {
     if (h->np <= 0) return hipSuccess;
     hipLaunchKernelGGL(k_fold_impulses, dim3((h->np + 63) / 64), dim3(64), 0, h->stream, h->b.part, h->cap, h->np,
-                       h->b.kpart, 1);
+                       h->b.kpart, particle_split(h->np));
     return hipGetLastError();
 }
 
@@ -889,7 +913,9 @@ hipError_t launch_clear_owner(lb_handle* h, uint32_t* owner) { return launch_fil
 
 hipError_t launch_raster(lb_handle* h, uint32_t* owner, int first, int count) {
     if (count <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_raster, dim3(count), dim3(kPB), 0, h->stream, h->box, h->b.part, h->cap, owner, first);
+    const int nsh = particle_split(count);
+    hipLaunchKernelGGL(k_raster, dim3(count * nsh), dim3(kPB), 0, h->stream, h->box, h->b.part, h->cap, owner, first,
+                       nsh);
     return hipGetLastError();
 }
 
@@ -898,17 +924,17 @@ hipError_t launch_killfill(lb_handle* h) {
     uint32_t* oo = h->b.owner[h->ocur];
     uint32_t* on = h->b.owner[1 - h->ocur];
     void* fn = h->b.f[1 - h->cur];
-    const int kext = kill_ext(h);
+    const int kext = kill_ext(h), nsh = particle_split(h->np);
     if (h->mom) {
-        hipLaunchKernelGGL(k_killfill_mom, dim3(h->np), dim3(kPB), 0, h->stream, h->box, h->b.mv[1 - h->mc],
-                           h->b.mv[h->mc], oo, on, h->b.part, h->cap, kext, h->b.kpart, h->b.health);
+        hipLaunchKernelGGL(k_killfill_mom, dim3(h->np * nsh), dim3(kPB), 0, h->stream, h->box, h->b.mv[1 - h->mc],
+                           h->b.mv[h->mc], oo, on, h->b.part, h->cap, kext, h->b.kpart, h->b.health, nsh);
         return hipGetLastError();
     }
     LBE_PDISPATCH(h->prm.precision,
-                  hipLaunchKernelGGL(k_killfill<P>, dim3(h->np), dim3(kPB), 0, h->stream, h->box,
+                  hipLaunchKernelGGL(k_killfill<P>, dim3(h->np * nsh), dim3(kPB), 0, h->stream, h->box,
                                      (typename P::S*)fn, oo, on, h->b.bmask[1 - h->cur], (typename P::R*)h->b.psi,
                                      (typename P::R*)h->b.rho,
-                                     h->b.part, h->cap, kext, h->b.kpart, h->b.health));
+                                     h->b.part, h->cap, kext, h->b.kpart, h->b.health, nsh));
     return hipGetLastError();
 }
 
@@ -917,15 +943,15 @@ hipError_t launch_killfill(lb_handle* h) {
 hipError_t launch_batch_shell(const BatchLaunch& bl, int precision, hipStream_t st, int o) {
     if (bl.n[BI_PART] == 0) return hipSuccess;
     if (precision == LB_FP64)
-        hipLaunchKernelGGL(k_shell_batch<double>, dim3(bl.n[BI_PART]), dim3(kPB), 0, st, bl.sys, bl.items[BI_PART], o);
+        hipLaunchKernelGGL(k_shell_batch<double>, dim3(bl.n[BI_SHARE]), dim3(kPB), 0, st, bl.sys, bl.items[BI_SHARE], o);
     else
-        hipLaunchKernelGGL(k_shell_batch<float>, dim3(bl.n[BI_PART]), dim3(kPB), 0, st, bl.sys, bl.items[BI_PART], o);
+        hipLaunchKernelGGL(k_shell_batch<float>, dim3(bl.n[BI_SHARE]), dim3(kPB), 0, st, bl.sys, bl.items[BI_SHARE], o);
     return hipGetLastError();
 }
 
 hipError_t launch_batch_forces(const BatchLaunch& bl, hipStream_t st) {
     if (bl.n[BI_PART] == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_linkforce_batch, dim3(bl.n[BI_PART]), dim3(kPB), 0, st, bl.sys, bl.items[BI_PART]);
+    hipLaunchKernelGGL(k_linkforce_batch, dim3(bl.n[BI_SHARE]), dim3(kPB), 0, st, bl.sys, bl.items[BI_SHARE]);
     return hipGetLastError();
 }
 
@@ -937,17 +963,17 @@ hipError_t launch_batch_bodies(const BatchLaunch& bl, hipStream_t st, int o) {
 
 hipError_t launch_batch_raster(const BatchLaunch& bl, hipStream_t st, int o) {
     if (bl.n[BI_PART] == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_raster_batch, dim3(bl.n[BI_PART]), dim3(kPB), 0, st, bl.sys, bl.items[BI_PART], o);
+    hipLaunchKernelGGL(k_raster_batch, dim3(bl.n[BI_SHARE]), dim3(kPB), 0, st, bl.sys, bl.items[BI_SHARE], o);
     return hipGetLastError();
 }
 
 hipError_t launch_batch_killfill(const BatchLaunch& bl, int precision, hipStream_t st, int oo, int fd) {
-    if (bl.n[BI_PART_POP] > 0)
-        LBE_PDISPATCH(precision, hipLaunchKernelGGL(k_killfill_batch<P>, dim3(bl.n[BI_PART_POP]), dim3(kPB), 0, st,
-                                                    bl.sys, bl.items[BI_PART_POP], oo, fd));
-    if (bl.n[BI_PART_MOM] > 0)
-        hipLaunchKernelGGL(k_killfill_mom_batch, dim3(bl.n[BI_PART_MOM]), dim3(kPB), 0, st, bl.sys,
-                           bl.items[BI_PART_MOM], oo);
+    if (bl.n[BI_SHARE_POP] > 0)
+        LBE_PDISPATCH(precision, hipLaunchKernelGGL(k_killfill_batch<P>, dim3(bl.n[BI_SHARE_POP]), dim3(kPB), 0, st,
+                                                    bl.sys, bl.items[BI_SHARE_POP], oo, fd));
+    if (bl.n[BI_SHARE_MOM] > 0)
+        hipLaunchKernelGGL(k_killfill_mom_batch, dim3(bl.n[BI_SHARE_MOM]), dim3(kPB), 0, st, bl.sys,
+                           bl.items[BI_SHARE_MOM], oo);
     return hipGetLastError();
 }
 

@@ -62,7 +62,7 @@ Layout layout_of(const lb_params* p) {
     const double rmax = p->max_particles > 0 ? p->max_radius : 0.5;
     const size_t kext = (size_t)killfill_extent(p->nx, p->ny, p->nz, rmax);
     L.rec = p->max_particles > 0 ? align_up(cap * kext * kext * kext * kRec * sizeof(double)) : 0;
-    L.kpart = align_up(cap * 8 * sizeof(double));
+    L.kpart = L.fpart = align_up((size_t)max_shares((int)cap) * 8 * sizeof(double));
     L.red = align_up((kRedBlocks + 1) * 8 * sizeof(double));
     L.counters = align_up(8 * sizeof(double));
     L.health = align_up(2 * sizeof(int));
@@ -71,7 +71,7 @@ Layout layout_of(const lb_params* p) {
     size_t ncell = 1;
     for (int d : {p->nx, p->ny, p->nz}) ncell *= (size_t)std::min(d, kMaxCellsPerAxis);
     L.cells = p->max_particles > 1 ? align_up((2 * ncell + 1 + 2 * cap) * sizeof(int)) : 0;
-    L.total = 2 * L.f + L.psi + L.rho + 2 * L.owner + 2 * L.bmask + L.part + 2 * L.pfast + L.rec + L.kpart + L.red +
+    L.total = 2 * L.f + L.psi + L.rho + 2 * L.owner + 2 * L.bmask + L.part + 2 * L.pfast + L.rec + L.kpart + L.fpart + L.red +
               L.counters + L.health + L.cells;
     return L;
 }
@@ -124,6 +124,7 @@ int setup_handle(lb_handle* h, const lb_params* prm, char* ws, size_t ws_bytes, 
     h->b.pfast[1] = (double*)p; p += L.pfast;
     h->b.rec = L.rec ? (double*)p : nullptr; p += L.rec;
     h->b.kpart = (double*)p; p += L.kpart;
+    h->b.fpart = (double*)p; p += L.fpart;
     h->b.red = (double*)p; p += L.red;
     h->b.counters = (double*)p; p += L.counters;
     h->b.health = (int*)p; p += L.health;
@@ -571,7 +572,8 @@ int lb_stats(lb_handle* h, double out[8]) {
     if (!h->inited) return fail(h, LB_ESTATE, "fields not initialised");
     LBE_HIP(h, launch_stats(h));
     double t[7], c0 = 0.0;
-    std::vector<double> km((size_t)h->np), fm((size_t)h->np), kp((size_t)h->np * 8);
+    const int sp = particle_split(h->np);
+    std::vector<double> km((size_t)h->np), fm((size_t)h->np), kp((size_t)h->np * sp * 8);
     LBE_HIP(h, hipMemcpyAsync(t, h->b.red + kRedBlocks * 8, 7 * sizeof(double), hipMemcpyDeviceToHost, h->stream));
     LBE_HIP(h, hipMemcpyAsync(&c0, h->b.counters, sizeof(double), hipMemcpyDeviceToHost, h->stream));
     if (h->np > 0) {
@@ -584,9 +586,15 @@ int lb_stats(lb_handle* h, double out[8]) {
     }
     LBE_HIP(h, hipStreamSynchronize(h->stream));
     // removed at placement, plus killed minus filled by each particle (the
-    // last step's amounts still wait in its kill/fill slot), in order
+    // last step's amounts still wait in its kill/fill slots), in order
     double removed = c0;
-    for (int k = 0; k < h->np; k++) removed += (km[k] + kp[8 * k + 6]) - (fm[k] + kp[8 * k + 7]);
+    for (int k = 0; k < h->np; k++) {
+        for (int s = 0; s < sp; s++) {
+            km[k] += kp[8 * ((size_t)k * sp + s) + 6];
+            fm[k] += kp[8 * ((size_t)k * sp + s) + 7];
+        }
+        removed += km[k] - fm[k];
+    }
     out[0] = t[0];
     out[1] = t[1];
     out[2] = t[2];
