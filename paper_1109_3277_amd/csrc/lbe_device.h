@@ -288,6 +288,7 @@ __device__ inline void pack_fast(const Box& bx, const double* part, int cap, int
 // block (or, for the row kernel, BY whole x-rows of BX = nx nodes).
 struct Tiles {
     int BX, BY, tiles_x, tiles_y;
+    bool rows = false;  // row kernel: every block whole x-rows of one plane
     bool zrun = false;  // tile kernel: walk z before y (see fused_body)
 };
 

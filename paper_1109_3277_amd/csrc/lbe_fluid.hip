@@ -1144,6 +1144,7 @@ Tiles fused_tiles(int nx, int ny, bool solids, int precision) {
     if (!solids && (precision != LB_FP64 || nx <= 128) &&
         ((nx == 64 && ny % 4 == 0) || (nx == 128 && ny % 2 == 0) || nx == 256 || nx == 512)) {
         // row kernel: whole x-rows per block
+        t.rows = true;
         t.BX = nx;
         t.BY = nx >= 256 ? 1 : 256 / nx;
         t.tiles_x = 1;
@@ -1170,7 +1171,7 @@ static void launch_fused_t(lb_handle* h, const Tiles& tl, unsigned grid) {
     auto fd = (typename P::S*)h->b.f[d];
     auto ps = (const typename P::R*)h->b.psi;
     const uint32_t* ow = h->b.owner[h->ocur];
-    if (!SOLID && tl.tiles_x == 1 && tl.BX >= 64 && tl.BX == h->box.nx) {
+    if (!SOLID && tl.rows) {
         const dim3 blk(tl.BX * tl.BY);
         switch (tl.BX) {
             case 64:
