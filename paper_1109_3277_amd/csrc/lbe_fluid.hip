@@ -706,9 +706,11 @@ __global__ __launch_bounds__(256, sizeof(typename P::R) == 8 ? 2 : (sizeof(typen
                                  d.kext * d.kext * d.kext, d.tiles_x, d.tiles_y, w.local, false);
 }
 
-// Row kernel for boxes without solids (nx a multiple of 64): a block holds
-// ROWS whole x-rows of one z-plane (NXT = nx nodes each). Because a block owns
-// complete rows, every push can be written aligned: the value a lane stores at
+// Row kernel for boxes without solids (nx a multiple of 64 up to 512): a block
+// holds ROWS whole x-rows of one z-plane (NXT = nx nodes each), 192 to 512
+// threads. HBM bounds it: pushes shifted by one node cost a plain push of 38
+// planes a quarter of its rate (256^3, 4 bytes: 4.0 against 5.0 TB/s). Because a
+// block owns complete rows, every push can be written aligned: the value a lane stores at
 // x comes from the source node x - c_ix, one lane over (wave shuffle; the wave
 // edges through LDS, rows wrapping periodically inside the block). Psi of the
 // rows y-1 .. y+ROWS in planes z-1..z+1 is staged in LDS.
@@ -722,7 +724,7 @@ __global__ __launch_bounds__(NXT * ROWS, NXT * ROWS == 256 ? (sizeof(typename P:
     constexpr int NW = NT / 64;         // waves per block
     constexpr int WPR = NXT / 64;       // waves per row
     constexpr int LR = (ROWS + 2) * 3;  // staged rows
-    static_assert(NXT % 64 == 0 && NT >= 256 && NT <= 1024, "row kernel shape");
+    static_assert(NXT % 64 == 0 && NT >= 192 && NT <= 512, "row kernel shape");
     __shared__ R s_psi[2][LR * NXT];
     // wave-edge values of the 10 directions with c_ix != 0: [wave][slot][comp]
     __shared__ R s_edge[NW][10][2];
@@ -1141,12 +1143,14 @@ Tiles fused_tiles(int nx, int ny, bool solids, int precision) {
     // up to 128 nodes (three waves per SIMD; 128^3: 0.236 against 0.245 ms).
     // Wider FP64 rows and boxes with solids use the tile kernel (256^3 FP64:
     // 2.09 against 2.17 ms for the row kernel).
-    if (!solids && (precision != LB_FP64 || nx <= 128) &&
-        ((nx == 64 && ny % 4 == 0) || (nx == 128 && ny % 2 == 0) || nx == 256 || nx == 512)) {
+    // A row of 192, 320, 384 or 448 nodes is a block of its own, as one of 256 or
+    // 512 is (192^3 FP32: 0.420 against 0.458 ms in tiles of 64 x 4).
+    if (!solids && (precision != LB_FP64 || nx <= 128) && nx % 64 == 0 && nx <= 512 &&
+        (nx > 128 || ny % (256 / nx) == 0)) {
         // row kernel: whole x-rows per block
         t.rows = true;
         t.BX = nx;
-        t.BY = nx >= 256 ? 1 : 256 / nx;
+        t.BY = nx > 128 ? 1 : 256 / nx;
         t.tiles_x = 1;
         t.tiles_y = ny / t.BY;
         return t;
@@ -1172,21 +1176,26 @@ static void launch_fused_t(lb_handle* h, const Tiles& tl, unsigned grid) {
     auto ps = (const typename P::R*)h->b.psi;
     const uint32_t* ow = h->b.owner[h->ocur];
     if (!SOLID && tl.rows) {
-        const dim3 blk(tl.BX * tl.BY);
-        switch (tl.BX) {
-            case 64:
-                hipLaunchKernelGGL((k_fused_rows<P, 64, 4>), dim3(grid), blk, 0, h->stream, h->box, fs, fd, ps);
-                break;
-            case 128:
-                hipLaunchKernelGGL((k_fused_rows<P, 128, 2>), dim3(grid), blk, 0, h->stream, h->box, fs, fd, ps);
-                break;
-            case 256:
-                hipLaunchKernelGGL((k_fused_rows<P, 256, 1>), dim3(grid), blk, 0, h->stream, h->box, fs, fd, ps);
-                break;
-            default:
-                hipLaunchKernelGGL((k_fused_rows<P, 512, 1>), dim3(grid), blk, 0, h->stream, h->box, fs, fd, ps);
-                break;
+#define LBE_LAUNCH_ROWS(NXT, ROWS) \
+    hipLaunchKernelGGL((k_fused_rows<P, NXT, ROWS>), dim3(grid), dim3(NXT * ROWS), 0, h->stream, h->box, fs, fd, ps)
+        if constexpr (std::is_same<P, PolF64>::value) {
+            if (tl.BX == 64)
+                LBE_LAUNCH_ROWS(64, 4);
+            else
+                LBE_LAUNCH_ROWS(128, 2);
+        } else {
+            switch (tl.BX) {
+                case 64: LBE_LAUNCH_ROWS(64, 4); break;
+                case 128: LBE_LAUNCH_ROWS(128, 2); break;
+                case 192: LBE_LAUNCH_ROWS(192, 1); break;
+                case 256: LBE_LAUNCH_ROWS(256, 1); break;
+                case 320: LBE_LAUNCH_ROWS(320, 1); break;
+                case 384: LBE_LAUNCH_ROWS(384, 1); break;
+                case 448: LBE_LAUNCH_ROWS(448, 1); break;
+                default: LBE_LAUNCH_ROWS(512, 1); break;
+            }
         }
+#undef LBE_LAUNCH_ROWS
         return;
     }
     const int ke = h->np > 0 ? kill_ext(h) : 0;

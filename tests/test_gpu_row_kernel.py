@@ -1,6 +1,7 @@
 """Particle-free boxes at the edges of the row kernel's rule: rows of 64 nodes
-whose count per plane does not fill whole blocks of four run in tiles. Against
-the oracle at the gates of the parity tests."""
+whose count per plane does not fill whole blocks of four run in tiles, and so
+do rows past 512 nodes; the other multiples of 64 are blocks of their own.
+Against the oracle at the gates of the parity tests."""
 import pytest
 
 from paper_1109_3277_amd.workloads import System, uniform_fields
@@ -10,7 +11,8 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("prec,tau,gate", [("fp64", 1.25, 1e-12), ("fp32", 1.0, 1e-5), ("fp16_dev", 1.0, 1e-3)])
-@pytest.mark.parametrize("dims", [(64, 6, 5), (64, 7, 4), (64, 5, 9)])
+@pytest.mark.parametrize("dims", [(64, 6, 5), (64, 7, 4), (64, 5, 9), (128, 5, 4), (192, 5, 7), (320, 4, 5), (384, 7, 4),
+                                  (448, 4, 5), (576, 4, 4)])
 def test_row_widths(dims, prec, tau, gate):
     ra, rb = uniform_fields(dims, sum(dims), 0.7, 0.7, 0.01)
     s = System(f"rows{dims}", dims, tau, 0.08, ra, rb)
