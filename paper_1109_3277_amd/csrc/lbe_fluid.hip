@@ -250,7 +250,7 @@ __device__ inline void fused_body(const Box& bx, const typename P::S* __restrict
                                   bool zrun) {
     using R = typename P::R;
     using S = typename P::S;
-    static_assert(BX * BY == 256, "one node per thread");
+    constexpr int NT = BX * BY;                            // one node per thread
     constexpr int TX = BX + 2, TY = BY + 2, TP = TX * TY;  // tile plane with a one-node halo
     __shared__ R s_psi[2][3 * TP];
     __shared__ uint32_t s_own[SOLID ? 3 * TP : 1];
@@ -341,12 +341,12 @@ __device__ inline void fused_body(const Box& bx, const typename P::S* __restrict
         }
     }
     // halo tile: every load of this thread issued before any is waited for
-    constexpr int NE = (3 * TP + 255) / 256;
+    constexpr int NE = (3 * TP + NT - 1) / NT;
     R t0[NE], t1[NE];
     uint32_t to[NE];
 #pragma unroll
     for (int k = 0; k < NE; k++) {
-        const int e = threadIdx.x + 256 * k;
+        const int e = threadIdx.x + NT * k;
         if (e < 3 * TP) {
             const int lz = e / TP, r = e - lz * TP, yy = r / TX, xx = r - yy * TX;
             // periodic wrap; positions past a ragged edge (only read by
@@ -365,7 +365,7 @@ __device__ inline void fused_body(const Box& bx, const typename P::S* __restrict
     }
 #pragma unroll
     for (int k = 0; k < NE; k++) {
-        const int e = threadIdx.x + 256 * k;
+        const int e = threadIdx.x + NT * k;
         if (e < 3 * TP) {
             s_psi[0][e] = t0[k];
             s_psi[1][e] = t1[k];
@@ -686,7 +686,7 @@ __device__ inline void fused_body(const Box& bx, const typename P::S* __restrict
 #undef LBE_OWN_OFFSETS
 }
 template <class P, bool SOLID, int BX, int BY>
-__global__ __launch_bounds__(256, sizeof(typename P::R) == 8 ? 2 : (sizeof(typename P::S) == 2 ? 4 : 3)) void k_fused(
+__global__ __launch_bounds__(BX * BY, BX * BY != 256 ? 1 : (sizeof(typename P::R) == 8 ? 2 : (sizeof(typename P::S) == 2 ? 4 : 3))) void k_fused(
     Box bx, const typename P::S* __restrict__ fs, typename P::S* __restrict__ fd, const typename P::R* __restrict__ psi,
     const uint32_t* __restrict__ owner, const uint32_t* __restrict__ bm_in, uint32_t* __restrict__ bm_out,
     const double* __restrict__ pfast, double* __restrict__ rec, int rstride, int tiles_x, int tiles_y, int zrun) {
@@ -706,9 +706,8 @@ __global__ __launch_bounds__(256, sizeof(typename P::R) == 8 ? 2 : (sizeof(typen
                                  d.kext * d.kext * d.kext, d.tiles_x, d.tiles_y, w.local, false);
 }
 
-// Row kernel for boxes without solids (nx a multiple of 64 up to 512): a block
-// holds ROWS whole x-rows of one z-plane (NXT = nx nodes each), 192 to 512
-// threads. HBM bounds it: pushes shifted by one node cost a plain push of 38
+// Row kernel for boxes without solids (nx 64, 128, 256 or 512): a block holds
+// ROWS whole x-rows of one z-plane (NXT = nx nodes each). HBM bounds it: pushes shifted by one node cost a plain push of 38
 // planes a quarter of its rate (256^3, 4 bytes: 4.0 against 5.0 TB/s). Because a
 // block owns complete rows, every push can be written aligned: the value a lane stores at
 // x comes from the source node x - c_ix, one lane over (wave shuffle; the wave
@@ -724,7 +723,7 @@ __global__ __launch_bounds__(NXT * ROWS, NXT * ROWS == 256 ? (sizeof(typename P:
     constexpr int NW = NT / 64;         // waves per block
     constexpr int WPR = NXT / 64;       // waves per row
     constexpr int LR = (ROWS + 2) * 3;  // staged rows
-    static_assert(NXT % 64 == 0 && NT >= 192 && NT <= 512, "row kernel shape");
+    static_assert(NXT % 64 == 0 && NT >= 256 && NT <= 512, "row kernel shape");
     __shared__ R s_psi[2][LR * NXT];
     // wave-edge values of the 10 directions with c_ix != 0: [wave][slot][comp]
     __shared__ R s_edge[NW][10][2];
@@ -1143,20 +1142,27 @@ Tiles fused_tiles(int nx, int ny, bool solids, int precision) {
     // up to 128 nodes (three waves per SIMD; 128^3: 0.236 against 0.245 ms).
     // Wider FP64 rows and boxes with solids use the tile kernel (256^3 FP64:
     // 2.09 against 2.17 ms for the row kernel).
-    // A row of 192, 320, 384 or 448 nodes is a block of its own, as one of 256 or
-    // 512 is (192^3 FP32: 0.420 against 0.458 ms in tiles of 64 x 4).
-    if (!solids && (precision != LB_FP64 || nx <= 128) && nx % 64 == 0 && nx <= 512 &&
-        (nx > 128 || ny % (256 / nx) == 0)) {
+    if (!solids && (precision != LB_FP64 || nx <= 128) &&
+        ((nx == 64 && ny % 4 == 0) || (nx == 128 && ny % 2 == 0) || nx == 256 || nx == 512)) {
         // row kernel: whole x-rows per block
         t.rows = true;
         t.BX = nx;
-        t.BY = nx > 128 ? 1 : 256 / nx;
+        t.BY = nx >= 256 ? 1 : 256 / nx;
         t.tiles_x = 1;
         t.tiles_y = ny / t.BY;
         return t;
     }
-    t.BX = nx >= 64 ? 64 : 32;
-    t.BY = 256 / t.BX;
+    // FP32 without solids: the other rows of a multiple of 64 nodes are a tile each
+    // (192 to 448 threads). The arithmetic stays the tile kernel's, bit for bit,
+    // and the shifted pushes of a row end in the block that began it: 192^3 0.429
+    // against 0.454 ms in tiles of 64 x 4, 384 x 128 x 96 0.291 against 0.348,
+    // 320 x 128 x 96 0.230 against 0.239. Not FP64 (192^3: 0.951 against 0.880 ms,
+    // 384: 0.651 against 0.610) or FP16 (192^3: 0.256 against 0.235).
+    if (!solids && precision == LB_FP32 && nx > 128 && nx < 512 && nx % 64 == 0)
+        t.BX = nx;
+    else
+        t.BX = nx >= 64 ? 64 : 32;
+    t.BY = t.BX > 128 ? 1 : 256 / t.BX;
     t.tiles_x = (nx + t.BX - 1) / t.BX;
     t.tiles_y = (ny + t.BY - 1) / t.BY;
     // z-runs pay for 8- and 4-byte populations on planes of many tiles
@@ -1178,36 +1184,35 @@ static void launch_fused_t(lb_handle* h, const Tiles& tl, unsigned grid) {
     if (!SOLID && tl.rows) {
 #define LBE_LAUNCH_ROWS(NXT, ROWS) \
     hipLaunchKernelGGL((k_fused_rows<P, NXT, ROWS>), dim3(grid), dim3(NXT * ROWS), 0, h->stream, h->box, fs, fd, ps)
-        if constexpr (std::is_same<P, PolF64>::value) {
-            if (tl.BX == 64)
-                LBE_LAUNCH_ROWS(64, 4);
-            else
-                LBE_LAUNCH_ROWS(128, 2);
-        } else {
-            switch (tl.BX) {
-                case 64: LBE_LAUNCH_ROWS(64, 4); break;
-                case 128: LBE_LAUNCH_ROWS(128, 2); break;
-                case 192: LBE_LAUNCH_ROWS(192, 1); break;
-                case 256: LBE_LAUNCH_ROWS(256, 1); break;
-                case 320: LBE_LAUNCH_ROWS(320, 1); break;
-                case 384: LBE_LAUNCH_ROWS(384, 1); break;
-                case 448: LBE_LAUNCH_ROWS(448, 1); break;
-                default: LBE_LAUNCH_ROWS(512, 1); break;
-            }
+        switch (tl.BX) {
+            case 64: LBE_LAUNCH_ROWS(64, 4); break;
+            case 128: LBE_LAUNCH_ROWS(128, 2); break;
+            case 256: LBE_LAUNCH_ROWS(256, 1); break;
+            default: LBE_LAUNCH_ROWS(512, 1); break;
         }
 #undef LBE_LAUNCH_ROWS
         return;
     }
     const int ke = h->np > 0 ? kill_ext(h) : 0;
     const int rstride = ke * ke * ke;
+#define LBE_LAUNCH_FUSED(BX, BY)                                                                                         \
+    hipLaunchKernelGGL((k_fused<P, SOLID, BX, BY>), dim3(grid), dim3(BX * BY), 0, h->stream, h->box, fs, fd, ps, ow,     \
+                       h->b.bmask[h->cur], h->b.bmask[1 - h->cur], h->b.pfast[h->ocur], h->b.rec, rstride, tl.tiles_x, \
+                       tl.tiles_y, tl.zrun ? 1 : 0)
+    if constexpr (!SOLID && std::is_same<P, PolF32>::value) {
+        switch (tl.BX) {
+            case 192: LBE_LAUNCH_FUSED(192, 1); return;
+            case 320: LBE_LAUNCH_FUSED(320, 1); return;
+            case 384: LBE_LAUNCH_FUSED(384, 1); return;
+            case 448: LBE_LAUNCH_FUSED(448, 1); return;
+            default: break;
+        }
+    }
     if (tl.BX == 64)
-        hipLaunchKernelGGL((k_fused<P, SOLID, 64, 4>), dim3(grid), dim3(256), 0, h->stream, h->box, fs, fd, ps, ow,
-                           h->b.bmask[h->cur], h->b.bmask[1 - h->cur], h->b.pfast[h->ocur], h->b.rec, rstride, tl.tiles_x,
-                           tl.tiles_y, tl.zrun ? 1 : 0);
+        LBE_LAUNCH_FUSED(64, 4);
     else
-        hipLaunchKernelGGL((k_fused<P, SOLID, 32, 8>), dim3(grid), dim3(256), 0, h->stream, h->box, fs, fd, ps, ow,
-                           h->b.bmask[h->cur], h->b.bmask[1 - h->cur], h->b.pfast[h->ocur], h->b.rec, rstride, tl.tiles_x,
-                           tl.tiles_y, tl.zrun ? 1 : 0);
+        LBE_LAUNCH_FUSED(32, 8);
+#undef LBE_LAUNCH_FUSED
 }
 
 hipError_t launch_fused(lb_handle* h) {

@@ -1,7 +1,8 @@
-"""Particle-free boxes at the edges of the row kernel's rule: rows of 64 nodes
-whose count per plane does not fill whole blocks of four run in tiles, and so
-do rows past 512 nodes; the other multiples of 64 are blocks of their own.
-Against the oracle at the gates of the parity tests."""
+"""Particle-free boxes at the edges of the row rules: rows of 64 nodes whose
+count per plane does not fill whole blocks of four run in tiles, and so do rows
+past 512 nodes; in FP32 the other multiples of 64 are a tile each, bit for bit
+as a batch's tiles of 64. Against the oracle at the gates of the parity tests."""
+import numpy as np
 import pytest
 
 from paper_1109_3277_amd.workloads import System, uniform_fields
@@ -24,3 +25,12 @@ def test_row_widths(dims, prec, tau, gate):
         assert res["e_rho"] <= gate, res
     else:
         check(res, gate, particles=False)
+    if dims[0] in (192, 320, 384, 448):
+        from paper_1109_3277_amd.binding import Batch
+
+        b = Batch([{"dims": dims, "tau": tau, "g_br": 0.08, "psi_kind": s.psi_kind}], prec)
+        b[0].init_fields(ra, rb)
+        b.step(20)
+        assert all(np.array_equal(u, v) for u, v in zip(g.read_fields(), b[0].read_fields()))
+        b.close()
+    g.close()
