@@ -214,9 +214,10 @@ int lb_save_state(lb_handle* h, void* host_buf, size_t bytes);
 int lb_load_state(lb_handle* h, const void* host_buf, size_t bytes);
 
 /* Per-phase timing with HIP events recorded on the handle's stream around
- * every kernel launch of lb_step (phases: 0 densities, 1 shell fill, 2 fused
- * force/collide/stream with bounce-back, 3 particle force sums, 4 rigid
- * bodies, 5 raster (clear + rasterise), 6 kill / fill). lb_profile_enable(h, 1)
+ * every kernel launch of lb_step (phases: 0 densities, 1 shell fill with the
+ * clear of the next owner map, 2 fused force/collide/stream with bounce-back,
+ * 3 particle force sums, 4 rigid bodies, 5 raster, 6 kill / fill). FP64
+ * systems with tau = 1 form the next densities in phase 2 and have no phase 0. lb_profile_enable(h, 1)
  * starts a fresh record, 0 stops recording.
  * lb_profile_read waits for the recorded events and writes, per phase, the
  * summed milliseconds and the number of launches (arrays of LB_NPHASES). */

@@ -429,6 +429,13 @@ struct SysDev {
     int tiles_x, tiles_y;
     int kext;  // largest kill/fill box edge of a normal step
 };
+// The densities rho^c of a batched system are kept (written by the density
+// pass, read by the shell fills) exactly when a lone handle keeps them: the
+// system has solid nodes (particles or walls), Psi is not rho itself, and the
+// workspace holds the buffer.
+__device__ inline void* sys_rho(const SysDev& d) {  // (systems in populations)
+    return (d.rho && (d.np > 0 || d.box.walls != 0) && d.box.psi_kind != 0) ? d.rho : nullptr;
+}
 
 // A batched launch: block b works on item items[b] = (system, local block).
 struct WorkItem {

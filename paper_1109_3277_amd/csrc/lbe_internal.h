@@ -169,9 +169,6 @@ hipError_t launch_canonical(lb_handle* h);
 hipError_t launch_bodies(lb_handle* h);
 hipError_t launch_pack_fast(lb_handle* h);  // packed particle copy from the particle table
 hipError_t launch_raster(lb_handle* h, uint32_t* owner, int first, int count);
-hipError_t launch_clear_owner(lb_handle* h, uint32_t* owner);
-hipError_t launch_clear_keep_walls(lb_handle* h, uint32_t* dst, const uint32_t* cur);  // walls copied from cur
-hipError_t launch_wall_shell(lb_handle* h);  // Psi of wall nodes next to fluid
 hipError_t launch_killfill(lb_handle* h);
 hipError_t launch_fold_impulses(lb_handle* h);
 // The step in moments (lbe_moment.hip).

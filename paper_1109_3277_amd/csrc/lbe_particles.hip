@@ -148,6 +148,38 @@ __global__ __launch_bounds__(kPB) void k_raster_batch(const SysDev* __restrict__
 }
 
 // ---------------------------------------------------------------- S2
+// Sums s0, s1 of the densities of node (x, y, z)'s fluid neighbours over the 18
+// links, in link order; returns their number. dens(m, d0, d1) gives those of node m. The
+// 18 owner codes are loaded together, then the densities of the fluid ones
+// together: two round trips to memory, where a loop over the links makes up to 36.
+template <class R, class F>
+__device__ inline int fluid_neighbours(const Box& bx, const uint32_t* __restrict__ owner, int x, int y, int z, F dens,
+                                       R& s0, R& s1) {
+    uint32_t on[Q];
+    uint32_t mm[Q];
+    R d0[Q], d1[Q];
+#pragma unroll
+    for (int i = 1; i < Q; i++) {
+        mm[i] = upstream(bx.nx, bx.ny, bx.nz, x, y, z, opp(i));  // n + c_i
+        on[i] = owner[mm[i]];
+    }
+#pragma unroll
+    for (int i = 1; i < Q; i++) {
+        d0[i] = d1[i] = R(0);
+        if (on[i] == OWN_FLUID) dens(mm[i], d0[i], d1[i]);
+    }
+    s0 = s1 = R(0);
+    int k = 0;
+#pragma unroll
+    for (int i = 1; i < Q; i++) {
+        if (on[i] != OWN_FLUID) continue;
+        s0 += d0[i];
+        s1 += d1[i];
+        k++;
+    }
+    return k;
+}
+
 // Eq. (10): a node of particle p with fluid neighbours (over the 18 links)
 // takes their mean density; the particle colour is added to A if positive,
 // its magnitude to B if negative. Densities are recovered from the stored
@@ -196,33 +228,14 @@ __device__ inline void shell_body(const Box& bx, R* __restrict__ psi, const R* _
             const BoxWalk w(lo, sz, Ls, (int)s_list[j], 1);
             const int x = w.x(), y = w.y(), z = w.z();
             const int64_t n = node_index(bx, x, y, z);
-            // owner codes first; densities only of the fluid neighbours (the
-            // gathers, not their latency, bound this loop)
-            uint32_t on[Q];
-            int64_t mm[Q];
-            R d0[Q], d1[Q];
-#pragma unroll
-            for (int i = 1; i < Q; i++) {
-                mm[i] = node_index(bx, wrapc(x + cx(i), nx), wrapc(y + cy(i), ny), wrapc(z + cz(i), nz));
-                on[i] = owner[mm[i]];
-            }
-#pragma unroll
-            for (int i = 1; i < Q; i++) {
-                d0[i] = d1[i] = R(0);
-                if (on[i] == OWN_FLUID) {
-                    d0[i] = dens[mm[i]];
-                    d1[i] = dens[N + mm[i]];
-                }
-            }
-            R s0 = R(0), s1 = R(0);
-            int k = 0;
-#pragma unroll
-            for (int i = 1; i < Q; i++) {
-                if (on[i] != OWN_FLUID) continue;
-                s0 += d0[i];
-                s1 += d1[i];
-                k++;
-            }
+            R s0, s1;
+            const int k = fluid_neighbours<R>(
+                bx, owner, x, y, z,
+                [&](uint32_t m, R& a, R& b) {
+                    a = dens[m];
+                    b = dens[N + m];
+                },
+                s0, s1);
             if (k == 0) {
                 psi[n] = R(0);
                 psi[N + n] = R(0);
@@ -237,12 +250,60 @@ __device__ inline void shell_body(const Box& bx, R* __restrict__ psi, const R* _
         __syncthreads();  // the list is read before the next segment resets it
     }
 }
-template <class R, int PT>
+// Eq. (10) for a wall node (colour 0): one with fluid neighbours takes their mean
+// density, stored as Psi; 0 without. Densities of fluid nodes: the stored rho
+// where kept, else Psi itself (Psi = rho) or recovered from it.
+template <class R>
+__device__ inline void wall_shell_node(const Box& bx, R* __restrict__ psi, const R* __restrict__ rho,
+                                       const uint32_t* __restrict__ owner, int64_t n) {
+    const int64_t N = bx.N;
+    int x, y, z;
+    node_xyz(bx, (uint32_t)n, x, y, z);
+    const R* dens = bx.psi_kind != 0 && rho ? rho : psi;
+    R s0, s1;
+    const int k = fluid_neighbours<R>(
+        bx, owner, x, y, z,
+        [&](uint32_t m, R& a, R& b) {
+            a = dens[m];
+            b = dens[N + m];
+            if (bx.psi_kind != 0 && !rho) {
+                a = rho_kept_of_psi(a, 1, R(bx.eref[0]));
+                b = rho_kept_of_psi(b, 1, R(bx.eref[1]));
+            }
+        },
+        s0, s1);
+    psi[n] = k == 0 ? R(0) : psi_kept(s0 / R(k), bx.psi_kind, R(bx.eref[0]));
+    psi[N + n] = k == 0 ? R(0) : psi_kept(s1 / R(k), bx.psi_kind, R(bx.eref[1]));
+}
+// The shell fills of a lone system and the owner copy that its moved particles are
+// to be drawn into, in one launch: blocks below np * nsh take the particles,
+// the others the box's nodes, which are independent of them: each is cleared in
+// owner_next (walls stay; none without particles) and filled if it is a wall node.
+// Short kernels of a small box wait on memory and cost a launch each: on the
+// 64^3 box of one ellipsoid between walls shell fill, wall fill and clear took 13.6,
+// 9.5 and 4.9 us one after the other, and take 13.8 together (walls alone, 353,024
+// nodes: 9.6 to 6.4). Many particles are bound by their gathers, and the clear runs beside
+// them (512 x 512 x 320: 570 and 54 us, now 610; 256^3 in FP16: 152 and 20, now 160):
+// without walls the kernel is built without their 30 registers in FP64, which cost a
+// wave per SIMD (702 us).
+template <class R, int PT, bool WALLS>
 __global__ __launch_bounds__(kPB) void k_shell(Box bx, R* __restrict__ psi, const R* __restrict__ rho,
-                                               const uint32_t* __restrict__ owner, const double* __restrict__ part,
-                                               int cap, int* __restrict__ suspect, int nsh) {
+                                               const uint32_t* __restrict__ owner, uint32_t* __restrict__ owner_next,
+                                               const double* __restrict__ part, int cap, int* __restrict__ suspect,
+                                               int np, int nsh) {
     if (blockIdx.x == 0 && threadIdx.x == 0) *suspect = 0;  // of the step that begins
-    shell_body<R, PT>(bx, psi, rho, owner, part, cap, blockIdx.x / nsh, blockIdx.x % nsh, nsh);
+    const int shares = np * nsh;
+    if ((int)blockIdx.x < shares) {
+        shell_body<R, PT>(bx, psi, rho, owner, part, cap, blockIdx.x / nsh, blockIdx.x % nsh, nsh);
+        return;
+    }
+    const int64_t stride = (int64_t)(gridDim.x - shares) * kPB;
+    for (int64_t n = (int64_t)(blockIdx.x - shares) * kPB + threadIdx.x; n < bx.N; n += stride) {
+        const bool wall = WALLS && owner[n] == OWN_WALL;
+        if (np > 0) owner_next[n] = wall ? OWN_WALL : OWN_FLUID;
+        if constexpr (WALLS)
+            if (wall) wall_shell_node<R>(bx, psi, rho, owner, n);
+    }
 }
 template <class R>
 __global__ __launch_bounds__(kPB) void k_shell_batch(const SysDev* __restrict__ sd, const WorkItem* __restrict__ items,
@@ -253,6 +314,19 @@ __global__ __launch_bounds__(kPB) void k_shell_batch(const SysDev* __restrict__ 
     R* psi = d.mom ? (R*)(d.mv[o] + 5 * d.box.N) : (R*)d.psi;  // (moments: R is double)
     const R* rho = d.mom ? (const R*)d.mv[o] : (const R*)d.rho;
     shell_body<R, kShellShort>(d.box, psi, rho, d.owner[o], d.part, d.cap, p, sh, nsh);
+}
+
+template <class R>
+__global__ __launch_bounds__(256) void k_wall_shell_batch(const SysDev* __restrict__ sd,
+                                                          const WorkItem* __restrict__ items, int o) {
+    const WorkItem w = items[blockIdx.x];
+    const SysDev& d = sd[w.sys];
+    if (d.box.walls == 0) return;
+    const int64_t n = (int64_t)w.local * 256 + threadIdx.x;
+    if (n >= d.box.N || d.owner[o][n] != OWN_WALL) return;
+    R* psi = d.mom ? (R*)(d.mv[o] + 5 * d.box.N) : (R*)d.psi;  // (moments: R is double)
+    const R* rho = d.mom ? (const R*)d.mv[o] : (const R*)sys_rho(d);
+    wall_shell_node<R>(d.box, psi, rho, d.owner[o], n);
 }
 
 // ---------------------------------------------------------------- S6 forces
@@ -866,19 +940,24 @@ int killfill_extent(int nx, int ny, int nz, double rb) {
 }
 int kill_ext(const lb_handle* h) { return killfill_extent(h->box.nx, h->box.ny, h->box.nz, h->rmax); }
 
-template <class R, int PT>
+template <class R, int PT, bool WALLS>
 static void launch_shell_t(lb_handle* h, int nsh) {
-    hipLaunchKernelGGL((k_shell<R, PT>), dim3(h->np * nsh), dim3(kPB), 0, h->stream, h->box, (R*)psi_now(h),
-                       (const R*)(h->mom ? rho_now(h) : h->b.rho), h->b.owner[h->ocur], h->b.part, h->cap,
-                       h->b.health + 1, nsh);
+    const int64_t nodes = std::min<int64_t>((h->box.N + kPB - 1) / kPB, 65536);
+    hipLaunchKernelGGL((k_shell<R, PT, WALLS>), dim3((unsigned)(h->np * nsh + nodes)), dim3(kPB), 0, h->stream, h->box,
+                       (R*)psi_now(h), (const R*)rho_now(h), h->b.owner[h->ocur], h->b.owner[1 - h->ocur], h->b.part,
+                       h->cap, h->b.health + 1, h->np, nsh);
+}
+template <class R>
+static void launch_shell_r(lb_handle* h, int nsh) {
+    if (h->box.walls)
+        nsh == 1 ? launch_shell_t<R, kShellLong, true>(h, nsh) : launch_shell_t<R, kShellShort, true>(h, nsh);
+    else
+        nsh == 1 ? launch_shell_t<R, kShellLong, false>(h, nsh) : launch_shell_t<R, kShellShort, false>(h, nsh);
 }
 hipError_t launch_shell(lb_handle* h) {
-    if (h->np <= 0) return hipSuccess;
+    if (h->np <= 0 && !h->box.walls) return hipSuccess;
     const int nsh = particle_split(h->np);
-    if (h->prm.precision == LB_FP64)
-        nsh == 1 ? launch_shell_t<double, kShellLong>(h, nsh) : launch_shell_t<double, kShellShort>(h, nsh);
-    else
-        nsh == 1 ? launch_shell_t<float, kShellLong>(h, nsh) : launch_shell_t<float, kShellShort>(h, nsh);
+    h->prm.precision == LB_FP64 ? launch_shell_r<double>(h, nsh) : launch_shell_r<float>(h, nsh);
     return hipGetLastError();
 }
 
@@ -908,8 +987,6 @@ hipError_t launch_fold_impulses(lb_handle* h) {
                        h->b.kpart, particle_split(h->np));
     return hipGetLastError();
 }
-
-hipError_t launch_clear_owner(lb_handle* h, uint32_t* owner) { return launch_fill_u32(h, owner, OWN_FLUID, h->box.N); }
 
 hipError_t launch_raster(lb_handle* h, uint32_t* owner, int first, int count) {
     if (count <= 0) return hipSuccess;
@@ -946,6 +1023,15 @@ hipError_t launch_batch_shell(const BatchLaunch& bl, int precision, hipStream_t 
         hipLaunchKernelGGL(k_shell_batch<double>, dim3(bl.n[BI_SHARE]), dim3(kPB), 0, st, bl.sys, bl.items[BI_SHARE], o);
     else
         hipLaunchKernelGGL(k_shell_batch<float>, dim3(bl.n[BI_SHARE]), dim3(kPB), 0, st, bl.sys, bl.items[BI_SHARE], o);
+    return hipGetLastError();
+}
+hipError_t launch_batch_wall_shell(const BatchLaunch& bl, int precision, hipStream_t st, int o) {
+    if (precision == LB_FP64)
+        hipLaunchKernelGGL(k_wall_shell_batch<double>, dim3(bl.n[BI_NODE]), dim3(256), 0, st, bl.sys,
+                           bl.items[BI_NODE], o);
+    else
+        hipLaunchKernelGGL(k_wall_shell_batch<float>, dim3(bl.n[BI_NODE]), dim3(256), 0, st, bl.sys,
+                           bl.items[BI_NODE], o);
     return hipGetLastError();
 }
 

@@ -199,14 +199,10 @@ hipError_t mark(lb_handle* h, int phase, bool start) {
         LBE_HIP(h, mark(h, ph, false));         \
     } while (0)
 
-// Owner copy `on` cleared and the moved particles drawn into it.
+// The moved particles drawn into the other owner copy, cleared by the shell launch.
 int enqueue_raster(lb_handle* h) {
     uint32_t* on = h->b.owner[1 - h->ocur];
     LBE_HIP(h, mark(h, 5, true));
-    if (h->box.walls)
-        LBE_HIP(h, launch_clear_keep_walls(h, on, h->b.owner[h->ocur]));
-    else
-        LBE_HIP(h, launch_clear_owner(h, on));
     LBE_HIP(h, launch_raster(h, on, 0, h->np));
     LBE_HIP(h, mark(h, 5, false));
     return LB_OK;
@@ -218,8 +214,7 @@ int enqueue_raster(lb_handle* h) {
 int enqueue_mom_step(lb_handle* h) {
     const int rc = to_moments(h);
     if (rc != LB_OK) return rc;
-    if (h->np > 0) LBE_PHASE(h, 1, launch_shell(h));
-    if (h->box.walls) LBE_PHASE(h, 1, launch_wall_shell(h));
+    if (h->has_solid) LBE_PHASE(h, 1, launch_shell(h));
     LBE_PHASE(h, 2, launch_mstep(h));
     h->oprev = h->ocur;
     h->acc_prev[0] = h->box.ax;
@@ -247,8 +242,7 @@ int enqueue_step(lb_handle* h) {
     if (in_moments(h->prm)) return enqueue_mom_step(h);
     if (!h->dens_ready) LBE_PHASE(h, 0, launch_density(h, h->cur, h->ocur, -1));
     h->dens_ready = false;
-    if (h->np > 0) LBE_PHASE(h, 1, launch_shell(h));
-    if (h->box.walls) LBE_PHASE(h, 1, launch_wall_shell(h));
+    if (h->has_solid) LBE_PHASE(h, 1, launch_shell(h));
     LBE_PHASE(h, 2, launch_fused(h));
     if (h->np > 0) {
         LBE_PHASE(h, 3, launch_forces(h));
