@@ -183,7 +183,7 @@ int refresh(lb_handle* h) {
         columns += (int64_t)tx * ty;
         deep = std::max(deep, (int)q->box.nz);
     }
-    B->bl.zc = mstep_planes(columns, deep);
+    B->bl.zc = mstep_planes(columns, deep, true);
     B->bl.mom = columns > 0;
     for (int s = 0; s < nsys; s++) {
         lb_handle* q = B->subs[s];

@@ -180,7 +180,7 @@ inline bool in_moments(const lb_params& p) { return p.tau == 1.0 && p.precision 
 size_t moment_bytes(const lb_params* p);  // one copy of the moment state
 int to_moments(lb_handle* h);             // moments of copy mc valid
 int to_pops(lb_handle* h);                // populations of f[cur] valid, in plain form
-int mstep_planes(int64_t columns, int nz);
+int mstep_planes(int64_t columns, int nz, bool solids);
 hipError_t launch_mom_from_pops(lb_handle* h);  // populations of f[cur] -> moment copy mc
 hipError_t launch_expand(lb_handle* h);         // the current state as populations in plain form, into f[cur]
 hipError_t launch_mstep(lb_handle* h);

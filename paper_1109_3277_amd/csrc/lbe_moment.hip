@@ -30,6 +30,10 @@ __device__ inline int xcd_range(int b, int nb) {
 // k, of node k - 1 the ones coming from plane k, which completes it. So each
 // node's 38 equilibria are formed from at most two resident planes, and two
 // blocks fit a CU. The next plane's loads are in flight meanwhile.
+// Without solids a thread reads its nine sources of plane k once, for the three
+// nodes they stream to, and carries the sums of plane k + 1 along: the order of
+// each node's sum is the same, one plane of moments suffices, and three blocks fit
+// a CU (128^3: 95 us per step in two planes, 81 in one).
 //
 // With solids, a source n - c_i that is solid stands for a link of n into it:
 // the population is the node's own f*_l, l = ibar, bounced (Eq. (4)), plus
@@ -50,7 +54,7 @@ __device__ inline void mstep_body(const Box& bx, const double* __restrict__ vin,
     constexpr int NP = (PP + 255) / 256;                       // staged Psi per thread and component
     static_assert((MP + 255) / 256 == 2, "the ring fits one extra round");
     __shared__ double s_psi[3][2][PP];
-    __shared__ double s_m[2][10][MP];
+    __shared__ double s_m[SOLID ? 2 : 1][10][MP];
     __shared__ uint32_t s_own[SOLID ? 4 : 1][SOLID ? MP : 1];
 
     const int nx = bx.nx, ny = bx.ny, nz = bx.nz;
@@ -164,6 +168,8 @@ __device__ inline void mstep_body(const Box& bx, const double* __restrict__ vin,
     const int c = mi[0];
     MomSum sum;               // of the node of plane k - 1, then of plane k
     sum.clear();
+    MomSum ahead;             // without solids: of the node of plane k + 1, what leaves plane k
+    ahead.clear();
     uint32_t mask = 0u;       // bit i: source n - c_i of the node is solid
     bool fluid = false;
     double b0[5], b1[5];      // its bounced populations from the plane above
@@ -171,7 +177,7 @@ __device__ inline void mstep_body(const Box& bx, const double* __restrict__ vin,
     for (int k = zbeg - 1; k <= zend; k++) {
         __syncthreads();
         // post-collision moments of plane k
-        double(*mk)[MP] = s_m[k & 1];
+        double(*mk)[MP] = s_m[SOLID ? k & 1 : 0];
 #pragma unroll
         for (int r = 0; r < 2; r++) {
             if (r == 1 && !ring) break;
@@ -209,20 +215,47 @@ __device__ inline void mstep_body(const Box& bx, const double* __restrict__ vin,
         }
         __syncthreads();
 
-        double(*mb)[MP] = s_m[(k + 1) & 1];  // plane k - 1
+        double(*mb)[MP] = s_m[SOLID ? (k + 1) & 1 : 0];  // plane k - 1 (with solids)
         // both components' population i from the moments at position e of plane buffer m
         auto from = [&](double(*m)[MP], int e, int i, double& v0, double& v1) {
             v0 = pop_eq(i, m[0][e], m[1][e], i == 0 ? 0.0 : dir_dot<double>(i, m[2][e], m[3][e], m[4][e]));
             v1 = pop_eq(i, m[5][e], m[6][e], i == 0 ? 0.0 : dir_dot<double>(i, m[7][e], m[8][e], m[9][e]));
         };
+        MomSum here = ahead;  // without solids: of the node of plane k
+        if constexpr (!SOLID) {
+            // each of the nine sources in plane k is read once, for the nodes of planes
+            // k - 1, k and k + 1 that it streams to
+            ahead.clear();
+#pragma unroll
+            for (int j = 0; j < 9; j++) {
+                double v0, v1;
+                const int ih = sum_dir(5 + j), e = c - cy(ih) * MX - cx(ih);
+                if (j < 5) {
+                    const int id = sum_dir(14 + j % 5), iu = sum_dir(j % 5);
+                    from(mk, e, id, v0, v1);
+                    sum.add(id, v0, v1);
+                    from(mk, e, iu, v0, v1);
+                    ahead.add(iu, v0, v1);
+                }
+                from(mk, e, ih, v0, v1);
+                here.add(ih, v0, v1);
+                // one source at a time: all nine read ahead cost more registers than
+                // three waves per SIMD leave
+                asm volatile("" : "+v"(here.d0), "+v"(here.d1), "+v"(here.jx), "+v"(here.jy), "+v"(here.jz),
+                             "+v"(sum.d0), "+v"(sum.d1), "+v"(sum.jx), "+v"(sum.jy), "+v"(sum.jz), "+v"(ahead.d0),
+                             "+v"(ahead.d1), "+v"(ahead.jx), "+v"(ahead.jy), "+v"(ahead.jz)
+                             :
+                             : "memory");
+            }
+        }
         // node of plane k - 1: the directions with c_iz = -1 come from plane k
         if (k > zbeg) {
 #pragma unroll
-            for (int j = 14; j < Q; j++) {
+            for (int j = 14; SOLID && j < Q; j++) {
                 const int i = sum_dir(j);
                 double v0, v1;
                 from(mk, c - cy(i) * MX - cx(i), i, v0, v1);
-                if (SOLID && ((mask >> i) & 1u)) {
+                if ((mask >> i) & 1u) {
                     v0 = b0[j - 14];
                     v1 = b1[j - 14];
                 }
@@ -242,8 +275,8 @@ __device__ inline void mstep_body(const Box& bx, const double* __restrict__ vin,
                 for (int f = 0; f < kMomPlanes; f++) *atw(vout + (size_t)f * N, b) = v[f];
             }
         }
-        // node of plane k: the directions with c_iz = +1 (from plane k - 1) and 0
-        if (k >= zbeg && more) {
+        if (SOLID && k >= zbeg && more) {
+            // node of plane k: the directions with c_iz = +1 (from plane k - 1) and 0
             sum.clear();
             auto own_at = [&](int i) -> uint32_t { return s_own[(k - cz(i)) & 3][c - cy(i) * MX - cx(i)]; };
             uint32_t top = 0u;
@@ -255,7 +288,7 @@ __device__ inline void mstep_body(const Box& bx, const double* __restrict__ vin,
                 top = fluid ? top : 0u;
             }
             mask = 0u;
-            if (!SOLID || __ballot(top != 0u) == 0ull) {
+            if (__ballot(top != 0u) == 0ull) {
 #pragma unroll
                 for (int j = 0; j < 14; j++) {
                     const int i = sum_dir(j);
@@ -441,6 +474,7 @@ __device__ inline void mstep_body(const Box& bx, const double* __restrict__ vin,
                 }
             }
         }
+        if constexpr (!SOLID) sum = here;
         if (more) {
             put_psi(sm);  // plane k + 2 takes the slot of plane k - 1, read before the last barrier
             put_own(k + 2);
@@ -452,7 +486,7 @@ __device__ inline void mstep_body(const Box& bx, const double* __restrict__ vin,
     }
 }
 template <bool SOLID, int TX>
-__global__ __launch_bounds__(256, 2) void k_mstep(Box bx, const double* __restrict__ vin, double* __restrict__ vout,
+__global__ __launch_bounds__(256, SOLID ? 2 : 3) void k_mstep(Box bx, const double* __restrict__ vin, double* __restrict__ vout,
                                                   const uint32_t* __restrict__ owner, const double* __restrict__ pfast,
                                                   double* __restrict__ rec, int rstride, int* __restrict__ bad,
                                                   int tiles_x, int tiles_y, int zc) {
@@ -461,7 +495,7 @@ __global__ __launch_bounds__(256, 2) void k_mstep(Box bx, const double* __restri
 }
 // Batched: item = (system, column); moment, owner and packed-particle copy c.
 template <bool SOLID, int TX>
-__global__ __launch_bounds__(256, 2) void k_mstep_batch(const SysDev* __restrict__ sd,
+__global__ __launch_bounds__(256, SOLID ? 2 : 3) void k_mstep_batch(const SysDev* __restrict__ sd,
                                                         const WorkItem* __restrict__ items, int c, int zc) {
     const WorkItem w = items[xcd_range(blockIdx.x, gridDim.x)];
     const SysDev& d = sd[w.sys];
@@ -613,11 +647,11 @@ __global__ __launch_bounds__(256) void k_mom_stats(Box bx, const double* __restr
 // ---------------------------------------------------------------- launchers
 static inline unsigned nblk(int64_t n) { return (unsigned)((n + 255) / 256); }
 
-// Planes a block marches: the fewest rounds of resident blocks (two per CU) times
-// the planes each works through (two more than it writes, and a start-up worth
-// about one).
-int mstep_planes(int64_t columns, int nz) {
-    constexpr int64_t resident = 512;
+// Planes a block marches: the fewest rounds of resident blocks (two per CU with
+// solids, three without) times the planes each works through (two more than it
+// writes, and a start-up worth about one).
+int mstep_planes(int64_t columns, int nz, bool solids) {
+    const int64_t resident = solids ? 512 : 768;
     int best = nz;
     double cost = 1e300;
     for (int chunks = 1; chunks <= nz; chunks++) {
@@ -649,7 +683,7 @@ hipError_t launch_expand(lb_handle* h) {
 hipError_t launch_mstep(lb_handle* h) {
     constexpr int W = 32;
     const int tx = (h->box.nx + W - 1) / W, ty = (h->box.ny + 256 / W - 1) / (256 / W);
-    const int zc = mstep_planes((int64_t)tx * ty, h->box.nz);
+    const int zc = mstep_planes((int64_t)tx * ty, h->box.nz, h->has_solid);
     const dim3 grid((unsigned)(tx * ty * ((h->box.nz + zc - 1) / zc)));
     const int ke = h->np > 0 ? kill_ext(h) : 0;
     int* bad = h->np > 0 ? h->b.health + 1 : h->b.health;
