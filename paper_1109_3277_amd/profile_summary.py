@@ -109,7 +109,8 @@ def traffic(args):
     cal_f, cal_w = fetch[CALIB][-1], write[CALIB][-1]
     ff = args.copy_bytes / (cal_f * 1024.0)
     wf = args.copy_bytes / (cal_w * 1024.0)
-    src = os.path.join(HERE, "csrc", "lbe_fluid.hip")
+    name = "lbe_moment.hip" if "mstep" in args.kernel else "lbe_fluid.hip"
+    src = os.path.join(HERE, "csrc", name)
     sha = hashlib.sha256(open(src, "rb").read()).hexdigest()[:16]
     print(f"# HBM traffic per kernel: {args.workload}, {args.precision}\n")
     print("Two counter passes (one counter each), from the repository root:\n")
@@ -117,7 +118,7 @@ def traffic(args):
         print(f"    {c}")
     print(f"\nCalibration: the same runs end with {CALIB} over {args.copy_bytes / 2 ** 30:.0f} GiB "
           f"(read once, written once). FETCH_SIZE reads {cal_f:.0f} KiB for it (factor {ff:.5f}), "
-          f"WRITE_SIZE {cal_w:.0f} KiB (factor {wf:.5f}). Source hash of lbe_fluid.hip: {sha}.\n")
+          f"WRITE_SIZE {cal_w:.0f} KiB (factor {wf:.5f}). Source hash of {name}: {sha}.\n")
     print("| kernel | dispatches | FETCH_SIZE KiB (mean) | WRITE_SIZE KiB (mean) | read GB | write GB |")
     print("|---|---|---|---|---|---|")
     for k in sorted(set(fetch) | set(write)):
