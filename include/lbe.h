@@ -208,7 +208,9 @@ int lb_set_static_solid(lb_handle* h, const uint8_t* mask, const double* wall_u)
  * handle created with the same parameters. The populations are stored in
  * plain form (each node's values in its own slots; between steps the values
  * bounced into solid nodes are kept there): saving rewrites the device state
- * into that form, which leaves every later result unchanged bit for bit. */
+ * into that form, which leaves every later result unchanged bit for bit. FP64
+ * systems with tau = 1 step in moments (densities, velocity, Psi); saving forms
+ * their populations beside them, and a loaded state goes on bit for bit. */
 size_t lb_state_bytes(const lb_handle* h);
 int lb_save_state(lb_handle* h, void* host_buf, size_t bytes);
 int lb_load_state(lb_handle* h, const void* host_buf, size_t bytes);
@@ -217,8 +219,8 @@ int lb_load_state(lb_handle* h, const void* host_buf, size_t bytes);
  * every kernel launch of lb_step (phases: 0 densities, 1 shell fill with the
  * clear of the next owner map, 2 fused force/collide/stream with bounce-back,
  * 3 particle force sums, 4 rigid bodies, 5 raster, 6 kill / fill). FP64
- * systems with tau = 1 form the next densities in phase 2 and have no phase 0. lb_profile_enable(h, 1)
- * starts a fresh record, 0 stops recording.
+ * systems with tau = 1 form the next densities in phase 2 and have no phase 0.
+ * lb_profile_enable(h, 1) starts a fresh record, 0 stops recording.
  * lb_profile_read waits for the recorded events and writes, per phase, the
  * summed milliseconds and the number of launches (arrays of LB_NPHASES). */
 #define LB_NPHASES 7
