@@ -170,14 +170,10 @@ int refresh(lb_handle* h) {
     B->h_sys.resize(nsys);
     B->walls = false;
     for (int k = 0; k < BI_COUNT; k++) B->h_items[k].clear();
-    // systems with tau = 1 go over to moments here
     int64_t columns = 0;
     int deep = 1;
     for (lb_handle* q : B->subs) {
-        if (!in_moments(q->prm)) continue;
-        q->mc = B->parity;
-        const int rc = to_moments(q);
-        if (rc != LB_OK) return fail(h, rc, q->err);
+        if (!q->mom) continue;
         int tx, ty;
         tiles_for(q->prm, B->bx, tx, ty);
         columns += (int64_t)tx * ty;
@@ -325,10 +321,6 @@ int batch_step_async(lb_handle* h, int nsteps) {
         if (q->mom) {
             q->mc = B->parity;
             q->oprev = 1 - B->parity;
-            q->pops = false;
-            q->acc_prev[0] = q->box.ax;
-            q->acc_prev[1] = q->box.ay;
-            q->acc_prev[2] = q->box.az;
         } else {
             q->cur = B->parity;
             q->dens_ready = true;
@@ -562,13 +554,10 @@ int lb_batch_tune(lb_handle* h, lb_tune_result* out) {
         LBE_HIP_OR_FAIL(h, hipEventCreate(&e1));
         float best = 0.0f;
         te.bx = B->bx;
-        // (a moment state goes through its populations, which the timed launches
-        // leave alone, and comes back bit for bit)
-        for (lb_handle* q : B->subs) {
-            const int r = to_pops(q);
-            if (r != LB_OK) return fail(h, r, q->err);
-            q->mom = q->mom && !in_moments(q->prm);
-        }
+        // (in moments it writes the copy from which a checkpoint would form the
+        // populations: they are formed first)
+        for (lb_handle* q : B->subs)
+            if (q->mom) LBE_HIP_OR_FAIL(h, launch_expand(q));
         for (int k = 0; k < LB_TUNE_CANDIDATES && rc == LB_OK; k++) {
             B->bx = kTileWidths[k];
             rc = refresh(h);
@@ -601,7 +590,10 @@ int lb_batch_tune(lb_handle* h, lb_tune_result* out) {
         for (lb_handle* q : B->subs) {
             const size_t rb = layout_of(&q->prm).rec;
             if (rb) LBE_HIP_OR_FAIL(h, launch_fill_f64(h, q->b.rec, 0.0, (int64_t)(rb / sizeof(double))));
-            LBE_HIP_OR_FAIL(h, launch_fill_u32(h, (uint32_t*)q->b.health + 1, 0u, 1));  // nor has a step been suspect
+            if (!q->mom) continue;
+            LBE_HIP_OR_FAIL(h, launch_fill_u32(h, (uint32_t*)q->b.health + ST_SUSPECT, 0u, 1));
+            LBE_HIP_OR_FAIL(h, launch_fill_u32(h, (uint32_t*)q->b.health + ST_FROM, FROM_POPS, 1));
+            LBE_HIP_OR_FAIL(h, launch_fill_u32(h, (uint32_t*)q->b.health + ST_BAD_START, 0u, 1));
         }
         std::lock_guard<std::mutex> lk(tune_mutex());
         tune_cache()[key] = te;

@@ -437,6 +437,23 @@ __device__ inline void* sys_rho(const SysDev& d) {  // (systems in populations)
     return (d.rho && (d.np > 0 || d.box.walls != 0) && d.box.psi_kind != 0) ? d.rho : nullptr;
 }
 
+// Status words of a system. The moment step (lbe_moment.h) keeps there what its
+// state came from, so that a recorded step that is replayed leaves the same trace
+// as one that is called.
+enum StatusWord : int {
+    ST_HEALTH = 0,     // nonzero once a NaN / negative density was seen (1) or a particle moved too far (2)
+    ST_SUSPECT = 1,    // the step in progress left a bad density on some node
+    ST_FROM = 2,       // where the current moments come from (StateFrom)
+    ST_BAD_START = 3,  // a state that was set, not stepped to, has a bad density on a fluid node
+    ST_ACC = 4,        // three doubles: body acceleration of the last step
+};
+constexpr int kStatusWords = 10;
+enum StateFrom : int {
+    FROM_FIELDS = 0,  // fields: the other moment copy holds each node's densities and velocity as given
+    FROM_POPS = 1,    // populations: those in f[0] are the state in plain form
+    FROM_STEP = 2,    // a step: the other moment copy, owner map and packed particles are those it started from
+};
+
 // A batched launch: block b works on item items[b] = (system, local block).
 struct WorkItem {
     int sys;

@@ -1043,6 +1043,7 @@ static inline unsigned nblk(int64_t n, int t = 256) { return (unsigned)((n + t -
     }
 
 hipError_t launch_init(lb_handle* h, const double* ra, const double* rb, const double* u) {
+    if (h->mom) return launch_mom_init(h, ra, rb, u);
     LBE_DISPATCH(h->prm.precision,
                  hipLaunchKernelGGL(k_init<P>, dim3(nblk(h->box.N)), dim3(256), 0, h->stream, h->box,
                                     (typename P::S*)h->b.f[h->cur], ra, rb, u, h->b.owner[h->ocur]));

@@ -27,7 +27,7 @@ struct Buffers {
     double* fpart = nullptr;           // link force and torque of the step, 8 (6 used) per particle and share
     double* red = nullptr;             // reduction partials, kRedBlocks x 8, then totals
     double* counters = nullptr;        // [0] fluid mass removed at particle placement (cumulative)
-    int* health = nullptr;             // [0] nonzero once a NaN / negative density was seen, [1] a step's suspicion
+    int* health = nullptr;             // status words (StatusWord)
     int* cells = nullptr;              // pair cell list: counts, starts, cell of each particle, list
 };
 
@@ -80,13 +80,13 @@ struct lb_handle {
     bool inited = false;
     bool has_solid = false;
     bool dens_ready = false;  // Psi (and rho) of the current populations already computed (end of the last step)
-    // tau = 1, FP64: the state lives in moments from the first step on. `cur` then
-    // stays 0, populations are held in f[0] and the moments in f[1].
-    bool mom = false;         // the moments of copy mc are the current state
-    bool pops = true;         // the populations of f[cur] are the current state too
+    // tau = 1, FP64: the state is the moments of copy mc, in f[1]; `cur` stays 0, and
+    // f[0] takes populations when a checkpoint needs them. A step launches the same
+    // kernels whatever came before it: what the state came from is a status word
+    // on the device, set where fields or a checkpoint are written.
+    bool mom = false;
     int mc = 0;               // current moment copy
     int oprev = 0;            // owner copy of the step that led to the current state
-    double acc_prev[3] = {0.0, 0.0, 0.0};  // and its body acceleration
     std::string err;
     // phase timing (lb_profile_*)
     bool prof_on = false;
@@ -178,10 +178,9 @@ hipError_t launch_fold_impulses(lb_handle* h);
 // ellipsoids 19.4 -> 8.3 ms.
 inline bool in_moments(const lb_params& p) { return p.tau == 1.0 && p.precision == LB_FP64; }
 size_t moment_bytes(const lb_params* p);  // one copy of the moment state
-int to_moments(lb_handle* h);             // moments of copy mc valid
-int to_pops(lb_handle* h);                // populations of f[cur] valid, in plain form
 int mstep_planes(int64_t columns, int nz, bool solids);
-hipError_t launch_mom_from_pops(lb_handle* h);  // populations of f[cur] -> moment copy mc
+hipError_t launch_mom_init(lb_handle* h, const double* d_rho_a, const double* d_rho_b, const double* d_u);
+hipError_t launch_mom_from_pops(lb_handle* h);  // populations of f[cur], in plain form, become the state
 hipError_t launch_expand(lb_handle* h);         // the current state as populations in plain form, into f[cur]
 hipError_t launch_mstep(lb_handle* h);
 hipError_t launch_mom_fields(lb_handle* h, double* ra, double* rb, double* u);

@@ -120,15 +120,15 @@ __device__ inline bool finish_node(const Box& bx, const MomSum& m, double (&v)[k
     return !(m.d0 >= 0.0) || !(m.d1 >= 0.0);
 }
 
-// A filled node (kill / fill): every population of both components is the
-// equilibrium of its density at velocity u.
-__device__ inline void fill_node(const Box& bx, double r0, double r1, const double (&u)[3], double (&v)[kMomPlanes]) {
+// A filled node (kill / fill, initial fields): every population of both components
+// is the equilibrium of its density at velocity u. True for a bad density.
+__device__ inline bool fill_node(const Box& bx, double r0, double r1, const double (&u)[3], double (&v)[kMomPlanes]) {
     const Post A = post_of(r0, u[0], u[1], u[2]), B = post_of(r1, u[0], u[1], u[2]);
     MomSum m;
     m.clear();
 #pragma unroll
     for (int k = 0; k < Q; k++) m.add(sum_dir(k), pop_of(A, sum_dir(k)), pop_of(B, sum_dir(k)));
-    (void)finish_node(bx, m, v);
+    return finish_node(bx, m, v);
 }
 
 // C of Eq. (4) per unit density for a link along c_l into a surface moving at U.

@@ -485,12 +485,23 @@ __device__ inline void mstep_body(const Box& bx, const double* __restrict__ vin,
         sp = s;
     }
 }
+// What the step leaves on record for a checkpoint (one thread per system), and
+// the verdict on a state that was set instead of stepped to.
+__device__ inline void begin_mstep(const Box& bx, int* __restrict__ status) {
+    if (status[ST_FROM] != FROM_STEP && status[ST_BAD_START] != 0) atomicOr(status + ST_HEALTH, 1);
+    status[ST_FROM] = FROM_STEP;
+    double* acc = (double*)(status + ST_ACC);
+    acc[0] = bx.ax;
+    acc[1] = bx.ay;
+    acc[2] = bx.az;
+}
 template <bool SOLID, int TX>
 __global__ __launch_bounds__(256, SOLID ? 2 : 3) void k_mstep(Box bx, const double* __restrict__ vin, double* __restrict__ vout,
                                                   const uint32_t* __restrict__ owner, const double* __restrict__ pfast,
-                                                  double* __restrict__ rec, int rstride, int* __restrict__ bad,
-                                                  int tiles_x, int tiles_y, int zc) {
-    mstep_body<SOLID, TX, 256 / TX>(bx, vin, vout, owner, pfast, rec, rstride, bad, tiles_x, tiles_y, zc,
+                                                  double* __restrict__ rec, int rstride, int* __restrict__ status,
+                                                  int bad, int tiles_x, int tiles_y, int zc) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) begin_mstep(bx, status);
+    mstep_body<SOLID, TX, 256 / TX>(bx, vin, vout, owner, pfast, rec, rstride, status + bad, tiles_x, tiles_y, zc,
                                     xcd_range(blockIdx.x, gridDim.x));
 }
 // Batched: item = (system, column); moment, owner and packed-particle copy c.
@@ -499,17 +510,42 @@ __global__ __launch_bounds__(256, SOLID ? 2 : 3) void k_mstep_batch(const SysDev
                                                         const WorkItem* __restrict__ items, int c, int zc) {
     const WorkItem w = items[xcd_range(blockIdx.x, gridDim.x)];
     const SysDev& d = sd[w.sys];
+    if (w.local == 0 && threadIdx.x == 0) begin_mstep(d.box, d.health);
     mstep_body<SOLID, TX, 256 / TX>(d.box, d.mv[c], d.mv[1 - c], d.owner[c], d.pfast[c], d.rec,
-                                    d.kext * d.kext * d.kext, d.health + 1, d.tiles_x, d.tiles_y, zc, w.local);
+                                    d.kext * d.kext * d.kext, d.health + ST_SUSPECT, d.tiles_x, d.tiles_y, zc, w.local);
 }
 
 // ---------------------------------------------------------------- conversions
-// Moments from populations in plain form (initial fields, a loaded state). The
-// first density check of a run happens here.
+// Moments from fields: every population of a fluid node is the equilibrium of its
+// density at velocity u, of which the sums are kept, as of a filled node; its
+// densities and velocity as given go to the other copy, v0, for a checkpoint that
+// is taken before the first step. 140 B per node, where populations take 352, and 368
+// more to sum them later.
+__global__ __launch_bounds__(256) void k_mom_init(Box bx, const double* __restrict__ ra, const double* __restrict__ rb,
+                                                  const double* __restrict__ u, const uint32_t* __restrict__ owner,
+                                                  double* __restrict__ v, double* __restrict__ v0,
+                                                  int* __restrict__ status) {
+    const size_t N = (size_t)bx.N;
+    const uint32_t n = blockIdx.x * 256u + threadIdx.x;
+    if (n >= N) return;
+    double out[kMomPlanes] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+    const double r0 = ra[n], r1 = rb[n];
+    double un[3] = {0.0, 0.0, 0.0};
+    if (u)
+        for (int d = 0; d < 3; d++) un[d] = u[3 * (size_t)n + d];
+    if (owner[n] == OWN_FLUID && fill_node(bx, r0, r1, un, out)) atomicOr(status + ST_BAD_START, 1);
+#pragma unroll
+    for (int p = 0; p < kMomPlanes; p++) v[(size_t)p * N + n] = out[p];
+    v0[n] = r0;
+    v0[N + n] = r1;
+    for (int d = 0; d < 3; d++) v0[(2 + d) * N + n] = un[d];
+}
+
+// Moments from populations in plain form (a loaded state).
 __global__ __launch_bounds__(256) void k_mom_from_pops(Box bx, const double* __restrict__ f,
                                                        const uint32_t* __restrict__ owner,
                                                        const uint32_t* __restrict__ bmask, double* __restrict__ v,
-                                                       int* __restrict__ health) {
+                                                       int* __restrict__ status) {
     const uint32_t N = (uint32_t)bx.N;
     const uint32_t n = blockIdx.x * 256u + threadIdx.x;
     if (n >= N) return;
@@ -528,7 +564,7 @@ __global__ __launch_bounds__(256) void k_mom_from_pops(Box bx, const double* __r
             pop_src(bx, n, x, y, z, bm, i, pi, s);
             m.add(i, f[(size_t)pi * N + s], f[(size_t)(Q + pi) * N + s]);
         }
-        if (finish_node(bx, m, out)) atomicOr(health, 1);
+        if (finish_node(bx, m, out)) atomicOr(status + ST_BAD_START, 1);
     }
 #pragma unroll
     for (int p = 0; p < kMomPlanes; p++) v[(size_t)p * N + n] = out[p];
@@ -551,13 +587,15 @@ __device__ inline void post_at(const Box& bx, const double* __restrict__ v, int 
 }
 
 // Populations of the current state in plain form, from the state one step
-// before (moment copy v0, owner map o0, packed particles pf0): each is formed as
-// the step formed it for its sums. Nodes filled since then hold the
-// equilibrium of the densities and velocity that kill / fill left in v0.
+// before (moment copy v0, owner map o0, packed particles pf0, acceleration in the
+// status words): each is formed as the step formed it for its sums. Nodes filled
+// since then hold the equilibrium of the densities and velocity that kill / fill
+// left in v0, and so do all nodes of a state set from fields. Populations that
+// were loaded are there already, but for nodes that particles have covered since.
 // Rare (checkpoints): nothing is staged.
 __global__ __launch_bounds__(256) void k_expand(Box bx, const double* __restrict__ v0, const uint32_t* __restrict__ o0,
                                                 const uint32_t* __restrict__ o1, const double* __restrict__ pf0,
-                                                double ax, double ay, double az, double* __restrict__ f,
+                                                const int* __restrict__ status, double* __restrict__ f,
                                                 uint32_t* __restrict__ bmask) {
     const size_t N = (size_t)bx.N;
     const uint32_t n = blockIdx.x * 256u + threadIdx.x;
@@ -565,8 +603,12 @@ __global__ __launch_bounds__(256) void k_expand(Box bx, const double* __restrict
     bmask[n] = 0u;
     int x, y, z;
     node_xyz(bx, n, x, y, z);
-    const bool fluid = o1[n] == OWN_FLUID, filled = fluid && o0[n] != OWN_FLUID;
-    const double acc[3] = {ax, ay, az};
+    const int from = status[ST_FROM];
+    const bool fluid = o1[n] == OWN_FLUID;
+    if (from == FROM_POPS && fluid) return;
+    const bool filled = fluid && (from == FROM_FIELDS || o0[n] != OWN_FLUID);
+    const double* accp = (const double*)(status + ST_ACC);
+    const double acc[3] = {accp[0], accp[1], accp[2]};
 #pragma unroll 1
     for (int i = 0; i < Q; i++) {
         double e0 = 0.0, e1 = 0.0;
@@ -606,10 +648,10 @@ __global__ __launch_bounds__(256) void k_expand(Box bx, const double* __restrict
 // in its kill / fill pass). It clears the flag for the next step.
 __global__ __launch_bounds__(256) void k_check_batch(const SysDev* __restrict__ sd, int c) {
     const SysDev& d = sd[blockIdx.x];
-    if (!d.mom || d.health[1] == 0) return;
-    check_suspect(d.box, d.mv[1 - c], d.owner[c], d.owner[1 - c], d.health + 1, d.health, 0, 1);
+    if (!d.mom || d.health[ST_SUSPECT] == 0) return;
+    check_suspect(d.box, d.mv[1 - c], d.owner[c], d.owner[1 - c], d.health + ST_SUSPECT, d.health, 0, 1);
     __syncthreads();
-    if (threadIdx.x == 0) d.health[1] = 0;
+    if (threadIdx.x == 0) d.health[ST_SUSPECT] = 0;
 }
 
 // ---------------------------------------------------------------- readout
@@ -666,7 +708,23 @@ int mstep_planes(int64_t columns, int nz, bool solids) {
     return best;
 }
 
+// Where the state comes from, and no bad density in it so far.
+static hipError_t set_from(lb_handle* h, StateFrom from) {
+    const hipError_t e = launch_fill_u32(h, (uint32_t*)h->b.health + ST_FROM, from, 1);
+    return e != hipSuccess ? e : launch_fill_u32(h, (uint32_t*)h->b.health + ST_BAD_START, 0u, 1);
+}
+
+hipError_t launch_mom_init(lb_handle* h, const double* ra, const double* rb, const double* u) {
+    const hipError_t e = set_from(h, FROM_FIELDS);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_mom_init, dim3(nblk(h->box.N)), dim3(256), 0, h->stream, h->box, ra, rb, u,
+                       h->b.owner[h->ocur], h->b.mv[h->mc], h->b.mv[1 - h->mc], h->b.health);
+    return hipGetLastError();
+}
+
 hipError_t launch_mom_from_pops(lb_handle* h) {
+    const hipError_t e = set_from(h, FROM_POPS);
+    if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_mom_from_pops, dim3(nblk(h->box.N)), dim3(256), 0, h->stream, h->box,
                        (const double*)h->b.f[h->cur], h->b.owner[h->ocur], h->b.bmask[h->cur], h->b.mv[h->mc],
                        h->b.health);
@@ -675,8 +733,8 @@ hipError_t launch_mom_from_pops(lb_handle* h) {
 
 hipError_t launch_expand(lb_handle* h) {
     hipLaunchKernelGGL(k_expand, dim3(nblk(h->box.N)), dim3(256), 0, h->stream, h->box, h->b.mv[1 - h->mc],
-                       h->b.owner[h->oprev], h->b.owner[h->ocur], h->b.pfast[h->oprev], h->acc_prev[0], h->acc_prev[1],
-                       h->acc_prev[2], (double*)h->b.f[h->cur], h->b.bmask[h->cur]);
+                       h->b.owner[h->oprev], h->b.owner[h->ocur], h->b.pfast[h->oprev], h->b.health,
+                       (double*)h->b.f[h->cur], h->b.bmask[h->cur]);
     return hipGetLastError();
 }
 
@@ -686,15 +744,15 @@ hipError_t launch_mstep(lb_handle* h) {
     const int zc = mstep_planes((int64_t)tx * ty, h->box.nz, h->has_solid);
     const dim3 grid((unsigned)(tx * ty * ((h->box.nz + zc - 1) / zc)));
     const int ke = h->np > 0 ? kill_ext(h) : 0;
-    int* bad = h->np > 0 ? h->b.health + 1 : h->b.health;
+    const int bad = h->np > 0 ? ST_SUSPECT : ST_HEALTH;
     const double* vin = h->b.mv[h->mc];
     double* vout = h->b.mv[1 - h->mc];
     if (h->has_solid)
         hipLaunchKernelGGL((k_mstep<true, W>), grid, dim3(256), 0, h->stream, h->box, vin, vout, h->b.owner[h->ocur],
-                           h->b.pfast[h->ocur], h->b.rec, ke * ke * ke, bad, tx, ty, zc);
+                           h->b.pfast[h->ocur], h->b.rec, ke * ke * ke, h->b.health, bad, tx, ty, zc);
     else
         hipLaunchKernelGGL((k_mstep<false, W>), grid, dim3(256), 0, h->stream, h->box, vin, vout, h->b.owner[h->ocur],
-                           h->b.pfast[h->ocur], h->b.rec, 0, bad, tx, ty, zc);
+                           h->b.pfast[h->ocur], h->b.rec, 0, h->b.health, bad, tx, ty, zc);
     return hipGetLastError();
 }
 

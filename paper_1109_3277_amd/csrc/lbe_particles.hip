@@ -777,7 +777,7 @@ __device__ inline void killfill_mom_node(const Box& bx, double* __restrict__ v, 
         const double ub[3] = {V[0] + (W[1] * r[2] - W[2] * r[1]), V[1] + (W[2] * r[0] - W[0] * r[2]),
                               V[2] + (W[0] * r[1] - W[1] * r[0])};
         double out[kMomPlanes];
-        fill_node(bx, rn[0], rn[1], ub, out);
+        (void)fill_node(bx, rn[0], rn[1], ub, out);
 #pragma unroll
         for (int k = 0; k < kMomPlanes; k++) v[(size_t)k * N + n] = out[k];
         v0[n] = rn[0];
@@ -906,7 +906,7 @@ __global__ __launch_bounds__(kPB, 3) void k_killfill_mom(Box bx, double* __restr
                                                          int nsh) {
     const int p = blockIdx.x / nsh;
     // (filled nodes are not fluid in own_old: the check and the fills do not meet)
-    check_suspect(bx, v, own_old, own_new, health + 1, health, blockIdx.x, gridDim.x);
+    check_suspect(bx, v, own_old, own_new, health + ST_SUSPECT, health, blockIdx.x, gridDim.x);
     killfill_body(bx, own_old, own_new, part, cap, kext, kpart, health, p, blockIdx.x % nsh, nsh,
                   [&](bool kill, int x, int y, int z, int64_t n, const double(&Xn)[3], double(&acc)[8]) {
                       killfill_mom_node(bx, v, v0, own_old, own_new, part, cap, p, kill, x, y, z, n, Xn, acc);
@@ -945,7 +945,7 @@ static void launch_shell_t(lb_handle* h, int nsh) {
     const int64_t nodes = std::min<int64_t>((h->box.N + kPB - 1) / kPB, 65536);
     hipLaunchKernelGGL((k_shell<R, PT, WALLS>), dim3((unsigned)(h->np * nsh + nodes)), dim3(kPB), 0, h->stream, h->box,
                        (R*)psi_now(h), (const R*)rho_now(h), h->b.owner[h->ocur], h->b.owner[1 - h->ocur], h->b.part,
-                       h->cap, h->b.health + 1, h->np, nsh);
+                       h->cap, h->b.health + ST_SUSPECT, h->np, nsh);
 }
 template <class R>
 static void launch_shell_r(lb_handle* h, int nsh) {

@@ -65,7 +65,7 @@ Layout layout_of(const lb_params* p) {
     L.kpart = L.fpart = align_up((size_t)max_shares((int)cap) * 8 * sizeof(double));
     L.red = align_up((kRedBlocks + 1) * 8 * sizeof(double));
     L.counters = align_up(8 * sizeof(double));
-    L.health = align_up(2 * sizeof(int));
+    L.health = align_up(kStatusWords * sizeof(int));
     // pair cell list: counts and starts of at most kMaxCellsPerAxis^3 cells
     // (one cell per node at most), the cell of each particle and the list
     size_t ncell = 1;
@@ -111,7 +111,8 @@ int setup_handle(lb_handle* h, const lb_params* prm, char* ws, size_t ws_bytes, 
     h->b.f[1] = p; p += L.f;
     // the moment state takes the place of the second population copy, 112 of its
     // 304 bytes per node
-    if (in_moments(*prm))
+    h->mom = in_moments(*prm);
+    if (h->mom)
         for (int k = 0; k < 2; k++) h->b.mv[k] = (double*)((char*)h->b.f[1] + k * moment_bytes(prm));
     h->b.psi = p; p += L.psi;
     h->b.rho = L.rho ? p : nullptr; p += L.rho;
@@ -142,22 +143,9 @@ int setup_handle(lb_handle* h, const lb_params* prm, char* ws, size_t ws_bytes, 
     if (L.rec) chk(launch_fill_f64(h, h->b.rec, 0.0, (int64_t)(L.rec / sizeof(double))), "clear link records");
     h->kpart_len = (int64_t)(L.kpart / sizeof(double));
     chk(launch_fill_f64(h, h->b.counters, 0.0, 8), "clear counters");
-    chk(launch_fill_u32(h, (uint32_t*)h->b.health, 0u, 2), "clear health");
+    chk(launch_fill_u32(h, (uint32_t*)h->b.health, 0u, kStatusWords), "clear status");
     chk(hipStreamSynchronize(h->stream), "synchronize");
     return rc;
-}
-
-int to_moments(lb_handle* h) {
-    if (h->mom) return LB_OK;
-    LBE_HIP(h, launch_mom_from_pops(h));
-    h->mom = true;
-    return LB_OK;
-}
-int to_pops(lb_handle* h) {
-    if (!h->mom || h->pops) return LB_OK;
-    LBE_HIP(h, launch_expand(h));
-    h->pops = true;
-    return LB_OK;
 }
 
 }  // namespace lbe
@@ -212,21 +200,15 @@ int enqueue_raster(lb_handle* h) {
 // the fluid pass itself, and nodes killed or filled by the re-rasterisation are
 // put right by kill / fill.
 int enqueue_mom_step(lb_handle* h) {
-    const int rc = to_moments(h);
-    if (rc != LB_OK) return rc;
     if (h->has_solid) LBE_PHASE(h, 1, launch_shell(h));
     LBE_PHASE(h, 2, launch_mstep(h));
     h->oprev = h->ocur;
-    h->acc_prev[0] = h->box.ax;
-    h->acc_prev[1] = h->box.ay;
-    h->acc_prev[2] = h->box.az;
-    h->pops = false;
     if (h->np > 0) {
         LBE_PHASE(h, 3, launch_forces(h));
         if (h->box.pairs) LBE_PHASE(h, 3, launch_pairs(h));
         LBE_PHASE(h, 4, launch_bodies(h));
-        const int r2 = enqueue_raster(h);
-        if (r2 != LB_OK) return r2;
+        const int rc = enqueue_raster(h);
+        if (rc != LB_OK) return rc;
         LBE_PHASE(h, 6, launch_killfill(h));
         h->ocur = 1 - h->ocur;
     }
@@ -239,7 +221,7 @@ int enqueue_mom_step(lb_handle* h) {
 // kill / fill reads its neighbours' densities instead of summing their
 // populations; the next step then starts from them.
 int enqueue_step(lb_handle* h) {
-    if (in_moments(h->prm)) return enqueue_mom_step(h);
+    if (h->mom) return enqueue_mom_step(h);
     if (!h->dens_ready) LBE_PHASE(h, 0, launch_density(h, h->cur, h->ocur, -1));
     h->dens_ready = false;
     if (h->has_solid) LBE_PHASE(h, 1, launch_shell(h));
@@ -336,8 +318,6 @@ int lb_init_fields(lb_handle* h, const double* rho_a, const double* rho_b, const
         h->box.rref[c] = h->box.rmean0[c];
         h->box.eref[c] = exp(-h->box.rref[c]);
     }
-    h->mom = false;  // the populations set here are the state
-    h->pops = true;
     double* st = (double*)staging(h);
     double* d_ra = st;
     double* d_rb = st + N;
@@ -386,8 +366,7 @@ int lb_add_ellipsoids(lb_handle* h, int32_t n, const double* radii, const double
     // plain form first: the removal below clears every solid node's slots,
     // where bounced populations of fluid neighbours may sit
     // (in moments a covered node's numbers are simply not read any more)
-    const bool pops_only = !h->mom;
-    if (pops_only) LBE_HIP(h, launch_canonical(h));
+    if (!h->mom) LBE_HIP(h, launch_canonical(h));
     if (h->mom && h->oprev == h->ocur) {
         // the map of the last step is kept: a checkpoint forms its populations with it
         LBE_HIP(h, launch_copy(h->b.owner[1 - h->ocur], h->b.owner[h->ocur],
@@ -439,12 +418,14 @@ int lb_add_ellipsoids(lb_handle* h, int32_t n, const double* radii, const double
     h->has_solid = true;
     LBE_HIP(h, launch_pack_fast(h));
     LBE_HIP(h, launch_raster(h, h->b.owner[h->ocur], first, n));
-    if (pops_only || h->pops) LBE_HIP(h, launch_remove_covered(h));
+    if (!h->mom) LBE_HIP(h, launch_remove_covered(h));
     LBE_HIP(h, launch_stats(h));
     LBE_HIP(h, hipMemcpyAsync(after, h->b.red + kRedBlocks * 8, 7 * sizeof(double), hipMemcpyDeviceToHost, h->stream));
     LBE_HIP(h, hipMemcpyAsync(&removed, h->b.counters, sizeof(double), hipMemcpyDeviceToHost, h->stream));
     LBE_HIP(h, hipStreamSynchronize(h->stream));
     removed += (before[0] + before[1]) - (after[0] + after[1]);
+    // a bad density that was set under the new particles is of no account
+    if (h->mom) LBE_HIP(h, launch_fill_u32(h, (uint32_t*)h->b.health + ST_BAD_START, after[6] > 0.0 ? 1u : 0u, 1));
     LBE_HIP(h, hipMemcpyAsync(h->b.counters, &removed, sizeof(double), hipMemcpyHostToDevice, h->stream));
     LBE_HIP(h, hipStreamSynchronize(h->stream));
     h->dens_ready = false;
@@ -672,12 +653,7 @@ int lb_save_state(lb_handle* h, void* host_buf, size_t bytes) {
     if (bytes < lb_state_bytes(h)) return fail(h, LB_EINVAL, "buffer too small");
     LBE_HIP(h, launch_fold_impulses(h));
     // the state is stored in plain form
-    if (h->mom) {
-        const int rc = to_pops(h);
-        if (rc != LB_OK) return rc;
-    } else {
-        LBE_HIP(h, launch_canonical(h));
-    }
+    LBE_HIP(h, h->mom ? launch_expand(h) : launch_canonical(h));
     const size_t N = (size_t)h->box.N;
     char* p = (char*)host_buf;
     double hdr[8] = {(double)h->np, h->box.rmean0[0], h->box.rmean0[1], h->box.rref[0], h->box.rref[1], h->rmax,
@@ -721,8 +697,6 @@ int lb_load_state(lb_handle* h, const void* host_buf, size_t bytes) {
             any_wall = any_wall || ow[n] == OWN_WALL;
         }
     }
-    h->mom = false;  // the populations loaded here are the state
-    h->pops = true;
     LBE_HIP(h, hipMemcpyAsync(h->b.f[h->cur], p, fb, hipMemcpyHostToDevice, h->stream));
     p += fb;
     LBE_HIP(h, hipMemcpyAsync(h->b.owner[h->ocur], p, N * sizeof(uint32_t), hipMemcpyHostToDevice, h->stream));
@@ -748,6 +722,7 @@ int lb_load_state(lb_handle* h, const void* host_buf, size_t bytes) {
     h->box.walls = !any_wall ? 0 : (moving ? 2 : 1);
     h->has_solid = h->np > 0 || any_wall;
     LBE_HIP(h, launch_pack_fast(h));
+    if (h->mom) LBE_HIP(h, launch_mom_from_pops(h));
     h->inited = true;
     h->dens_ready = false;
     batch_touch(h);
