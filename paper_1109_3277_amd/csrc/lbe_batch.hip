@@ -170,17 +170,19 @@ int refresh(lb_handle* h) {
     B->h_sys.resize(nsys);
     B->walls = false;
     for (int k = 0; k < BI_COUNT; k++) B->h_items[k].clear();
-    int64_t columns = 0;
-    int deep = 1;
+    // the systems without and with solids are a launch of the moment step each
+    int64_t columns[2] = {0, 0};
+    int deep[2] = {1, 1};
     for (lb_handle* q : B->subs) {
         if (!q->mom) continue;
         int tx, ty;
         tiles_for(q->prm, B->bx, tx, ty);
-        columns += (int64_t)tx * ty;
-        deep = std::max(deep, (int)q->box.nz);
+        const int k = q->has_solid ? 1 : 0;
+        columns[k] += (int64_t)tx * ty;
+        deep[k] = std::max(deep[k], (int)q->box.nz);
     }
-    B->bl.zc = mstep_planes(columns, deep, true);
-    B->bl.mom = columns > 0;
+    for (int k = 0; k < 2; k++) B->bl.zc[k] = mstep_planes(columns[k], deep[k], k == 1);
+    B->bl.mom = columns[0] + columns[1] > 0;
     for (int s = 0; s < nsys; s++) {
         lb_handle* q = B->subs[s];
         SysDev& d = B->h_sys[s];
@@ -190,7 +192,8 @@ int refresh(lb_handle* h) {
         d.kext = kill_ext(q);
         const int nnode = (int)((q->box.N + 255) / 256);
         const int ntile = d.tiles_x * d.tiles_y * q->box.nz;
-        const int ncol = d.tiles_x * d.tiles_y * ((q->box.nz + B->bl.zc - 1) / B->bl.zc);
+        const int zc = B->bl.zc[q->has_solid ? 1 : 0];
+        const int ncol = d.tiles_x * d.tiles_y * ((q->box.nz + zc - 1) / zc);
         for (int i = 0; i < nnode; i++) B->h_items[BI_NODE].push_back({s, i});
         for (int i = 0; i < q->np; i++) B->h_items[BI_PART].push_back({s, i});
         for (int i = 0; i < q->np * particle_split(q->np); i++) {

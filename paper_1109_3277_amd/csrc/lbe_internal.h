@@ -58,7 +58,7 @@ struct BatchLaunch {
     const WorkItem* items[BI_COUNT] = {};
     int n[BI_COUNT] = {};
     int bx = 64;  // fused tile width: 64 (64x4), 32 (32x8) or 16 (16x16)
-    int zc = 1;   // planes per block of the moment step
+    int zc[2] = {1, 1};  // planes per block of the moment step, without and with solids
     bool mom = false;  // some system advances in moments
 };
 
@@ -86,6 +86,7 @@ struct lb_handle {
     // on the device, set where fields or a checkpoint are written.
     bool mom = false;
     int mc = 0;               // current moment copy
+    int zc[2] = {1, 1};       // planes a block of the moment step marches, without and with solids
     int oprev = 0;            // owner copy of the step that led to the current state
     std::string err;
     // phase timing (lb_profile_*)
@@ -178,6 +179,7 @@ hipError_t launch_fold_impulses(lb_handle* h);
 // ellipsoids 19.4 -> 8.3 ms.
 inline bool in_moments(const lb_params& p) { return p.tau == 1.0 && p.precision == LB_FP64; }
 size_t moment_bytes(const lb_params* p);  // one copy of the moment state
+constexpr int kMomTileX = 32;             // columns of the moment step: 32 x 8 nodes
 int mstep_planes(int64_t columns, int nz, bool solids);
 hipError_t launch_mom_init(lb_handle* h, const double* d_rho_a, const double* d_rho_b, const double* d_u);
 hipError_t launch_mom_from_pops(lb_handle* h);  // populations of f[cur], in plain form, become the state

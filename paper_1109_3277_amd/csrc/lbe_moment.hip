@@ -691,19 +691,21 @@ static inline unsigned nblk(int64_t n) { return (unsigned)((n + 255) / 256); }
 
 // Planes a block marches: the fewest rounds of resident blocks (two per CU with
 // solids, three without) times the planes each works through (two more than it
-// writes, and a start-up worth about one).
+// writes, and a start-up worth about one). Looked for once per box, over the
+// values that ceil(nz / chunks) takes (some 2 sqrt(nz): going through every number of
+// chunks took 3.9 ms at nz = 2^20).
 int mstep_planes(int64_t columns, int nz, bool solids) {
     const int64_t resident = solids ? 512 : 768;
     int best = nz;
     double cost = 1e300;
-    for (int chunks = 1; chunks <= nz; chunks++) {
-        const int zc = (nz + chunks - 1) / chunks;
+    for (int zc = nz;; zc = (nz - 1) / ((nz + zc - 2) / (zc - 1)) + 1) {
         const int64_t blocks = columns * ((nz + zc - 1) / zc);
         const double c = (double)((blocks + resident - 1) / resident) * (zc + 3);
         if (c < cost) {
             cost = c;
             best = zc;
         }
+        if (zc == 1) break;
     }
     return best;
 }
@@ -739,9 +741,9 @@ hipError_t launch_expand(lb_handle* h) {
 }
 
 hipError_t launch_mstep(lb_handle* h) {
-    constexpr int W = 32;
+    constexpr int W = kMomTileX;
     const int tx = (h->box.nx + W - 1) / W, ty = (h->box.ny + 256 / W - 1) / (256 / W);
-    const int zc = mstep_planes((int64_t)tx * ty, h->box.nz, h->has_solid);
+    const int zc = h->zc[h->has_solid ? 1 : 0];
     const dim3 grid((unsigned)(tx * ty * ((h->box.nz + zc - 1) / zc)));
     const int ke = h->np > 0 ? kill_ext(h) : 0;
     const int bad = h->np > 0 ? ST_SUSPECT : ST_HEALTH;
@@ -771,15 +773,15 @@ hipError_t launch_mom_stats(lb_handle* h) {
 // ---------------------------------------------------------------- batched
 template <bool SOLID>
 static void launch_batch_mstep_t(const BatchLaunch& bl, hipStream_t st, int c) {
-    const int k = SOLID ? BI_MTILE : BI_MTILE_PLAIN;
+    const int k = SOLID ? BI_MTILE : BI_MTILE_PLAIN, zc = bl.zc[SOLID ? 1 : 0];
     if (bl.n[k] == 0) return;
     const dim3 grid(bl.n[k]);
     if (bl.bx == 64)
-        hipLaunchKernelGGL((k_mstep_batch<SOLID, 64>), grid, dim3(256), 0, st, bl.sys, bl.items[k], c, bl.zc);
+        hipLaunchKernelGGL((k_mstep_batch<SOLID, 64>), grid, dim3(256), 0, st, bl.sys, bl.items[k], c, zc);
     else if (bl.bx == 32)
-        hipLaunchKernelGGL((k_mstep_batch<SOLID, 32>), grid, dim3(256), 0, st, bl.sys, bl.items[k], c, bl.zc);
+        hipLaunchKernelGGL((k_mstep_batch<SOLID, 32>), grid, dim3(256), 0, st, bl.sys, bl.items[k], c, zc);
     else
-        hipLaunchKernelGGL((k_mstep_batch<SOLID, 16>), grid, dim3(256), 0, st, bl.sys, bl.items[k], c, bl.zc);
+        hipLaunchKernelGGL((k_mstep_batch<SOLID, 16>), grid, dim3(256), 0, st, bl.sys, bl.items[k], c, zc);
 }
 hipError_t launch_batch_mstep(const BatchLaunch& bl, hipStream_t st, int c) {
     launch_batch_mstep_t<true>(bl, st, c);

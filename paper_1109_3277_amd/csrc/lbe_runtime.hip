@@ -113,7 +113,11 @@ int setup_handle(lb_handle* h, const lb_params* prm, char* ws, size_t ws_bytes, 
     // 304 bytes per node
     h->mom = in_moments(*prm);
     if (h->mom)
-        for (int k = 0; k < 2; k++) h->b.mv[k] = (double*)((char*)h->b.f[1] + k * moment_bytes(prm));
+        for (int k = 0; k < 2; k++) {
+            h->b.mv[k] = (double*)((char*)h->b.f[1] + k * moment_bytes(prm));
+            constexpr int W = kMomTileX, H = 256 / W;
+            h->zc[k] = mstep_planes((int64_t)((b.nx + W - 1) / W) * ((b.ny + H - 1) / H), b.nz, k == 1);
+        }
     h->b.psi = p; p += L.psi;
     h->b.rho = L.rho ? p : nullptr; p += L.rho;
     h->b.owner[0] = (uint32_t*)p; p += L.owner;

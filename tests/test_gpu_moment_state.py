@@ -88,3 +88,30 @@ def test_moment_checkpoint(story, walls):
     assert _digest(a.save_state()) == _digest(b.save_state())
     a.close()
     b.close()
+
+
+def test_thin_box_enqueues_without_planning():
+    """A long thin box: the split of its planes over the blocks is not worked out
+    again on the host in every step (it was, plane count by plane count: some
+    4 ms a step here). Enqueueing a step takes a few microseconds; 1 ms allows
+    for a slow host."""
+    import time
+
+    import torch
+    from paper_1109_3277_amd.binding import Lattice
+
+    dims = (3, 3, 1 << 20)
+    g = Lattice(dims, 1.0, 0.08, 1, "fp64")
+    ra = np.full(g.N, 0.7)
+    g.init_fields(ra, ra)
+    g.step(2)
+    steps, best = 10, 1e9
+    for _ in range(3):
+        torch.cuda.synchronize()
+        t0 = time.perf_counter()
+        g.step_async(steps)
+        best = min(best, (time.perf_counter() - t0) / steps)
+    torch.cuda.synchronize()
+    log(f"  {1e6 * best:.1f} us per step to enqueue")
+    assert best < 1e-3
+    g.close()
