@@ -278,10 +278,11 @@ int lb_batch_system(lb_handle* batch, int32_t sys, lb_handle** out);
 /* Autotune the fused kernel's tile shape for this batch: each candidate
  * (BX x 256/BX nodes of one xy-plane per 256-thread block, BX in
  * tile_widths) is timed on the current state over all systems (the timed
- * launches only write the scratch population copy; the state does not
- * change) and the fastest is kept. The choice is cached for the life of the
- * process per precision and system shapes (box, solids or not); a batch of
- * the same shapes takes it without timing. Results do not depend on the
+ * launches only write the copy that the next step writes; the state and its
+ * checkpoints do not change) and the fastest is kept. The choice is cached for
+ * the life of the process per precision and system shapes (box, solids or
+ * not, and in FP64 whether tau = 1); a batch of the same shapes takes it
+ * without timing. Results do not depend on the
  * choice. Requires fields on every system. out (may be NULL) receives the
  * chosen width, whether it came from the cache, and each candidate's time
  * per fused launch over all systems in ms. */

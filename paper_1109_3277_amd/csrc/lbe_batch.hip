@@ -497,8 +497,9 @@ int lb_stats_sys(lb_handle* h, int32_t sys, double out[8]) {
 namespace {
 
 // Tuning results kept for the life of the process, keyed by the precision and
-// the shape of every system (box and whether it holds solids): a batch of the
-// same systems is not timed again.
+// the shape of every system (box, whether it holds solids, and whether it steps in
+// moments, which is another kernel): a batch of the same systems is not timed
+// again.
 struct TuneEntry {
     int bx;
     double ms[LB_TUNE_CANDIDATES];
@@ -515,7 +516,7 @@ std::string tune_key(const BatchState* B) {
     std::string k = std::to_string(B->precision);
     for (const lb_handle* q : B->subs)
         k += ";" + std::to_string(q->box.nx) + "x" + std::to_string(q->box.ny) + "x" + std::to_string(q->box.nz) +
-             (q->has_solid ? "s" : "f");
+             (q->has_solid ? "s" : "f") + (q->mom ? "m" : "");
     return k;
 }
 
