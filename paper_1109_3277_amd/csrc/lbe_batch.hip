@@ -67,7 +67,7 @@ void item_capacity(const lb_params& p, size_t cap[BI_COUNT]) {
     cap[BI_NODE_POP] = mom ? 0 : cap[BI_NODE];
     cap[BI_TILE] = cap[BI_TILE_PLAIN] = mom ? 0 : tiles;
     cap[BI_MTILE] = cap[BI_MTILE_PLAIN] = mom ? tiles : 0;
-    const size_t shares = np > 0 ? (size_t)max_shares((int)np) : 0;
+    const size_t shares = np > 0 ? max_shares(np) : 0;
     cap[BI_PART] = np;
     cap[BI_SHARE] = shares;
     cap[BI_SHARE_POP] = mom ? 0 : shares;

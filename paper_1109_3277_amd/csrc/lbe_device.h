@@ -11,6 +11,8 @@
 #include <hip/hip_bf16.h>
 #include <stdint.h>
 
+#include <algorithm>
+
 namespace lbe {
 
 constexpr int Q = 19;
@@ -306,10 +308,7 @@ __host__ __device__ inline int particle_split(int np) {
     return s < 1 ? 1 : (s > kMaxSplit ? kMaxSplit : s);
 }
 // Shares of all particles of a system, at most, for a capacity of cap.
-__host__ __device__ inline int max_shares(int cap) {
-    const int a = cap * kMaxSplit, b = cap > 1024 ? cap : 1024;
-    return a < b ? a : b;
-}
+inline size_t max_shares(size_t cap) { return std::min(cap * kMaxSplit, std::max<size_t>(cap, 1024)); }
 
 // Link records of a particle: one record of kRec doubles per node of its
 // record box (its bounding box grown by one node on every side, each edge at

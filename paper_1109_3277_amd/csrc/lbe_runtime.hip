@@ -62,7 +62,7 @@ Layout layout_of(const lb_params* p) {
     const double rmax = p->max_particles > 0 ? p->max_radius : 0.5;
     const size_t kext = (size_t)killfill_extent(p->nx, p->ny, p->nz, rmax);
     L.rec = p->max_particles > 0 ? align_up(cap * kext * kext * kext * kRec * sizeof(double)) : 0;
-    L.kpart = L.fpart = align_up((size_t)max_shares((int)cap) * 8 * sizeof(double));
+    L.kpart = L.fpart = align_up(max_shares(cap) * 8 * sizeof(double));
     L.red = align_up((kRedBlocks + 1) * 8 * sizeof(double));
     L.counters = align_up(8 * sizeof(double));
     L.health = align_up(kStatusWords * sizeof(int));
