@@ -106,7 +106,10 @@ int lb_add_ellipsoids(lb_handle* h, int32_t n, const double* radii, const double
  * rigid-body update, re-rasterisation with kill/fill). Work is enqueued on
  * the handle's stream; the call then waits for it to check the health flag and
  * returns LB_EUNSTABLE if a NaN or negative density appeared or if a particle
- * moved more than two lattice spacings in one step. */
+ * moved more than two lattice spacings in one step. The densities of the state
+ * that the last step ends in are looked at too where there are particles, and in
+ * FP64 at tau = 1; else those that each step starts from (the next call then
+ * reports what the last step made). */
 int lb_step(lb_handle* h, int32_t nsteps);
 
 /* Same as lb_step but does not wait: no health check; the stream is left
