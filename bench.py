@@ -15,7 +15,6 @@ largest single-GPU one: 512^3 with 41,802 ellipsoids in FP64.
 from __future__ import annotations
 
 import argparse
-import hashlib
 import json
 import os
 import sys
@@ -171,14 +170,14 @@ def roofline_of(s, prec, res, traffic):
 
 def measured_traffic(workload: str, prec: str, kind: str = "fused"):
     """HBM bytes per fused launch from the committed rocprofv3 PMC summary, if
-    it was taken on the current kernel source (else None)."""
+    it was taken on the kernel's current sources, headers included (else None)."""
+    from paper_1109_3277_amd.profile_summary import fluid_source, source_hash
+
     path = os.path.join(ROOT, "profiles", f"{kind}_{prec}_{workload}_pmc.json")
     if not os.path.exists(path):
         return None
     rec = json.load(open(path))
-    src = os.path.join(ROOT, "paper_1109_3277_amd", "csrc", "lbe_moment.hip" if prec == "fp64" else "lbe_fluid.hip")
-    h = hashlib.sha256(open(src, "rb").read()).hexdigest()[:16]
-    if rec.get("source_sha256_16") != h:
+    if rec.get("source_sha256_16") != source_hash(fluid_source(prec == "fp64")):
         return None
     return rec.get("bytes_per_launch")
 

@@ -12,8 +12,8 @@ run and tabulates calls and average / min / max duration per kernel.
 by the calibration kernel (k_probe_copy16) of a known number of bytes, whose
 counter readings give the factor from counter units to bytes; every kernel's
 per-dispatch readings are scaled by it. The JSON record carries the hash of the
-fused kernel's source, so that a reader can tell whether it still describes the
-current kernel.
+fused kernel's sources (its file and the headers that it includes), so that a
+reader can tell whether it still describes the current kernel.
 """
 from __future__ import annotations
 
@@ -28,6 +28,30 @@ import sys
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CALIB = "k_probe_copy16"
+
+
+def fluid_source(moments: bool) -> str:
+    """The file that holds the fluid kernel."""
+    return os.path.join(HERE, "csrc", "lbe_moment.hip" if moments else "lbe_fluid.hip")
+
+
+def source_hash(path: str) -> str:
+    """Hash of a source file and of all that it includes by a quoted name, each
+    once, in the order in which they are met."""
+    seen, h = [], hashlib.sha256()
+
+    def add(f):
+        f = os.path.realpath(f)
+        if f in seen:
+            return
+        seen.append(f)
+        data = open(f, "rb").read()
+        h.update(data)
+        for name in re.findall(rb'^\s*#\s*include\s*"([^"]+)"', data, flags=re.M):
+            add(os.path.join(os.path.dirname(f), name.decode()))
+
+    add(path)
+    return h.hexdigest()[:16]
 
 
 def _csvs(d, suffix):
@@ -109,16 +133,15 @@ def traffic(args):
     cal_f, cal_w = fetch[CALIB][-1], write[CALIB][-1]
     ff = args.copy_bytes / (cal_f * 1024.0)
     wf = args.copy_bytes / (cal_w * 1024.0)
-    name = "lbe_moment.hip" if "mstep" in args.kernel else "lbe_fluid.hip"
-    src = os.path.join(HERE, "csrc", name)
-    sha = hashlib.sha256(open(src, "rb").read()).hexdigest()[:16]
+    src = fluid_source("mstep" in args.kernel)
+    sha = source_hash(src)
     print(f"# HBM traffic per kernel: {args.workload}, {args.precision}\n")
     print("Two counter passes (one counter each), from the repository root:\n")
     for c in args.cmds:
         print(f"    {c}")
     print(f"\nCalibration: the same runs end with {CALIB} over {args.copy_bytes / 2 ** 30:.0f} GiB "
           f"(read once, written once). FETCH_SIZE reads {cal_f:.0f} KiB for it (factor {ff:.5f}), "
-          f"WRITE_SIZE {cal_w:.0f} KiB (factor {wf:.5f}). Source hash of {name}: {sha}.\n")
+          f"WRITE_SIZE {cal_w:.0f} KiB (factor {wf:.5f}). Source hash of {os.path.basename(src)} and its headers: {sha}.\n")
     print("| kernel | dispatches | FETCH_SIZE KiB (mean) | WRITE_SIZE KiB (mean) | read GB | write GB |")
     print("|---|---|---|---|---|---|")
     for k in sorted(set(fetch) | set(write)):
