@@ -596,8 +596,7 @@ int lb_batch_tune(lb_handle* h, lb_tune_result* out) {
             if (rb) LBE_HIP_OR_FAIL(h, launch_fill_f64(h, q->b.rec, 0.0, (int64_t)(rb / sizeof(double))));
             if (!q->mom) continue;
             LBE_HIP_OR_FAIL(h, launch_fill_u32(h, (uint32_t*)q->b.health + ST_SUSPECT, 0u, 1));
-            LBE_HIP_OR_FAIL(h, launch_fill_u32(h, (uint32_t*)q->b.health + ST_FROM, FROM_POPS, 1));
-            LBE_HIP_OR_FAIL(h, launch_fill_u32(h, (uint32_t*)q->b.health + ST_BAD_START, 0u, 1));
+            LBE_HIP_OR_FAIL(h, launch_set_from(q, FROM_POPS));
         }
         std::lock_guard<std::mutex> lk(tune_mutex());
         tune_cache()[key] = te;

@@ -448,8 +448,8 @@ enum StatusWord : int {
 };
 constexpr int kStatusWords = 10;
 enum StateFrom : int {
-    FROM_FIELDS = 0,  // fields: the other moment copy holds each node's densities and velocity as given
-    FROM_POPS = 1,    // populations: those in f[0] are the state in plain form
+    FROM_POPS = 0,    // populations: those in f[0] are the state in plain form
+    FROM_FIELDS = 1,  // fields: the other moment copy holds each node's densities and velocity as given
     FROM_STEP = 2,    // a step: the other moment copy, owner map and packed particles are those it started from
 };
 

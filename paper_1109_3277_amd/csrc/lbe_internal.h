@@ -182,7 +182,8 @@ size_t moment_bytes(const lb_params* p);  // one copy of the moment state
 constexpr int kMomTileX = 32;             // columns of the moment step: 32 x 8 nodes
 int mstep_planes(int64_t columns, int nz, bool solids);
 hipError_t launch_mom_init(lb_handle* h, const double* d_rho_a, const double* d_rho_b, const double* d_u);
-hipError_t launch_mom_from_pops(lb_handle* h);  // populations of f[cur], in plain form, become the state
+hipError_t launch_mom_from_pops(lb_handle* h);  // moment copy mc from the populations of f[cur], in plain form
+hipError_t launch_set_from(lb_handle* h, int from);  // a state that was set (StateFrom)
 hipError_t launch_expand(lb_handle* h);         // the current state as populations in plain form, into f[cur]
 hipError_t launch_mstep(lb_handle* h);
 hipError_t launch_mom_fields(lb_handle* h, double* ra, double* rb, double* u);

@@ -543,26 +543,19 @@ __global__ __launch_bounds__(256) void k_mom_init(Box bx, const double* __restri
 
 // Moments from populations in plain form (a loaded state).
 __global__ __launch_bounds__(256) void k_mom_from_pops(Box bx, const double* __restrict__ f,
-                                                       const uint32_t* __restrict__ owner,
-                                                       const uint32_t* __restrict__ bmask, double* __restrict__ v,
+                                                       const uint32_t* __restrict__ owner, double* __restrict__ v,
                                                        int* __restrict__ status) {
     const uint32_t N = (uint32_t)bx.N;
     const uint32_t n = blockIdx.x * 256u + threadIdx.x;
     if (n >= N) return;
     double out[kMomPlanes] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
     if (owner[n] == OWN_FLUID) {
-        const uint32_t bm = bmask[n];
-        int x, y, z;
-        node_xyz(bx, n, x, y, z);
         MomSum m;
         m.clear();
 #pragma unroll
         for (int k = 0; k < Q; k++) {
             const int i = sum_dir(k);
-            int pi;
-            uint32_t s;
-            pop_src(bx, n, x, y, z, bm, i, pi, s);
-            m.add(i, f[(size_t)pi * N + s], f[(size_t)(Q + pi) * N + s]);
+            m.add(i, f[(size_t)i * N + n], f[(size_t)(Q + i) * N + n]);
         }
         if (finish_node(bx, m, out)) atomicOr(status + ST_BAD_START, 1);
     }
@@ -592,15 +585,13 @@ __device__ inline void post_at(const Box& bx, const double* __restrict__ v, int 
 // since then hold the equilibrium of the densities and velocity that kill / fill
 // left in v0, and so do all nodes of a state set from fields. Populations that
 // were loaded are there already, but for nodes that particles have covered since.
-// Rare (checkpoints): nothing is staged.
+// Rare (checkpoints): nothing is staged. The directions are split over gridDim.y.
 __global__ __launch_bounds__(256) void k_expand(Box bx, const double* __restrict__ v0, const uint32_t* __restrict__ o0,
                                                 const uint32_t* __restrict__ o1, const double* __restrict__ pf0,
-                                                const int* __restrict__ status, double* __restrict__ f,
-                                                uint32_t* __restrict__ bmask) {
+                                                const int* __restrict__ status, double* __restrict__ f) {
     const size_t N = (size_t)bx.N;
     const uint32_t n = blockIdx.x * 256u + threadIdx.x;
     if (n >= N) return;
-    bmask[n] = 0u;
     int x, y, z;
     node_xyz(bx, n, x, y, z);
     const int from = status[ST_FROM];
@@ -610,7 +601,7 @@ __global__ __launch_bounds__(256) void k_expand(Box bx, const double* __restrict
     const double* accp = (const double*)(status + ST_ACC);
     const double acc[3] = {accp[0], accp[1], accp[2]};
 #pragma unroll 1
-    for (int i = 0; i < Q; i++) {
+    for (int i = blockIdx.y; i < Q; i += gridDim.y) {
         double e0 = 0.0, e1 = 0.0;
         if (filled) {
             const double ux = v0[2 * N + n], uy = v0[3 * N + n], uz = v0[4 * N + n];
@@ -711,13 +702,17 @@ int mstep_planes(int64_t columns, int nz, bool solids) {
 }
 
 // Where the state comes from, and no bad density in it so far.
-static hipError_t set_from(lb_handle* h, StateFrom from) {
-    const hipError_t e = launch_fill_u32(h, (uint32_t*)h->b.health + ST_FROM, from, 1);
-    return e != hipSuccess ? e : launch_fill_u32(h, (uint32_t*)h->b.health + ST_BAD_START, 0u, 1);
+__global__ void k_set_from(int* __restrict__ status, int from) {
+    status[ST_FROM] = from;
+    status[ST_BAD_START] = 0;
+}
+hipError_t launch_set_from(lb_handle* h, int from) {
+    hipLaunchKernelGGL(k_set_from, dim3(1), dim3(1), 0, h->stream, h->b.health, from);
+    return hipGetLastError();
 }
 
 hipError_t launch_mom_init(lb_handle* h, const double* ra, const double* rb, const double* u) {
-    const hipError_t e = set_from(h, FROM_FIELDS);
+    const hipError_t e = launch_set_from(h, FROM_FIELDS);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_mom_init, dim3(nblk(h->box.N)), dim3(256), 0, h->stream, h->box, ra, rb, u,
                        h->b.owner[h->ocur], h->b.mv[h->mc], h->b.mv[1 - h->mc], h->b.health);
@@ -725,18 +720,18 @@ hipError_t launch_mom_init(lb_handle* h, const double* ra, const double* rb, con
 }
 
 hipError_t launch_mom_from_pops(lb_handle* h) {
-    const hipError_t e = set_from(h, FROM_POPS);
-    if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_mom_from_pops, dim3(nblk(h->box.N)), dim3(256), 0, h->stream, h->box,
-                       (const double*)h->b.f[h->cur], h->b.owner[h->ocur], h->b.bmask[h->cur], h->b.mv[h->mc],
-                       h->b.health);
+                       (const double*)h->b.f[h->cur], h->b.owner[h->ocur], h->b.mv[h->mc], h->b.health);
     return hipGetLastError();
 }
 
 hipError_t launch_expand(lb_handle* h) {
-    hipLaunchKernelGGL(k_expand, dim3(nblk(h->box.N)), dim3(256), 0, h->stream, h->box, h->b.mv[1 - h->mc],
+    // a small box leaves most CUs idle with one thread per node, which works through
+    // 19 chains of loads (16^3: a save took 240 us, 180 in populations)
+    const unsigned nb = nblk(h->box.N);
+    hipLaunchKernelGGL(k_expand, dim3(nb, nb < 1024 ? Q : 1), dim3(256), 0, h->stream, h->box, h->b.mv[1 - h->mc],
                        h->b.owner[h->oprev], h->b.owner[h->ocur], h->b.pfast[h->oprev], h->b.health,
-                       (double*)h->b.f[h->cur], h->b.bmask[h->cur]);
+                       (double*)h->b.f[h->cur]);
     return hipGetLastError();
 }
 

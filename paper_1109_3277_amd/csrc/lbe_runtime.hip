@@ -709,8 +709,11 @@ int lb_load_state(lb_handle* h, const void* host_buf, size_t bytes) {
     LBE_HIP(h, hipMemcpyAsync(h->b.part, p, pb, hipMemcpyHostToDevice, h->stream));
     p += pb;
     LBE_HIP(h, hipMemcpyAsync(h->b.counters, p, 8 * sizeof(double), hipMemcpyHostToDevice, h->stream));
-    LBE_HIP(h, launch_fill_u32(h, (uint32_t*)h->b.health, 0u, 2));
-    LBE_HIP(h, launch_fill_u32(h, h->b.bmask[h->cur], 0u, (int64_t)N));  // stored in plain form
+    LBE_HIP(h, launch_fill_u32(h, (uint32_t*)h->b.health, 0u, ST_BAD_START + 1));  // (FROM_POPS is 0)
+    if (h->mom)
+        LBE_HIP(h, launch_mom_from_pops(h));
+    else
+        LBE_HIP(h, launch_fill_u32(h, h->b.bmask[h->cur], 0u, (int64_t)N));  // stored in plain form
     LBE_HIP(h, launch_fill_f64(h, h->b.kpart, 0.0, h->kpart_len));
     LBE_HIP(h, hipStreamSynchronize(h->stream));
     h->np = (int)hdr[0];
@@ -726,7 +729,6 @@ int lb_load_state(lb_handle* h, const void* host_buf, size_t bytes) {
     h->box.walls = !any_wall ? 0 : (moving ? 2 : 1);
     h->has_solid = h->np > 0 || any_wall;
     LBE_HIP(h, launch_pack_fast(h));
-    if (h->mom) LBE_HIP(h, launch_mom_from_pops(h));
     h->inited = true;
     h->dens_ready = false;
     batch_touch(h);
