@@ -113,7 +113,12 @@ int lb_add_ellipsoids(lb_handle* h, int32_t n, const double* radii, const double
 int lb_step(lb_handle* h, int32_t nsteps);
 
 /* Same as lb_step but does not wait: no health check; the stream is left
- * running (for timing and graph capture by the caller). */
+ * running (for timing and graph capture by the caller). A graph of an even
+ * number of steps of a lone handle may be replayed: each replay goes on from
+ * the state before it, with the particle count, body acceleration and mean
+ * densities that were current at its recording. After lb_init_fields or
+ * lb_load_state a graph goes on from the new state if the system is FP64 at
+ * tau = 1, or has no particles, or had not stepped when it was recorded. */
 int lb_step_async(lb_handle* h, int32_t nsteps);
 
 /* Macroscopic fields (Sec. 2, the moments defined after Eq. (2): rho^c =
@@ -190,8 +195,8 @@ int lb_set_body_accel(lb_handle* h, const double a[3]);
  * delta_c (taken no smaller than delta_c / 4), viscosity from the initial
  * mean densities. The paper uses K_H = 100 and delta_c = 2/3. The forces and
  * torques join the bounce-back sums at each rigid-body update; pairs are
- * found with a device cell list and summed in a fixed order. on = 0 turns
- * them off. LB_EINVAL for K_H < 0 or delta_c <= 0; LB_ESTATE on a batch or
+ * found among all particles, past 2048 of them with a device cell list, and
+ * summed in a fixed order. on = 0 turns them off. LB_EINVAL for K_H < 0 or delta_c <= 0; LB_ESTATE on a batch or
  * system handle, or when max_particles < 2. */
 int lb_set_pair_interactions(lb_handle* h, int on, double K_H, double delta_c);
 

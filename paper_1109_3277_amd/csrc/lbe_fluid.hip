@@ -700,12 +700,13 @@ __global__ __launch_bounds__(256, sizeof(typename P::R) == 8 ? 2 : (sizeof(typen
 }
 
 // Row kernel for boxes without solids (nx 64, 128, 256 or 512): a block holds
-// ROWS whole x-rows of one z-plane (NXT = nx nodes each). HBM bounds it: pushes shifted by one node cost a plain push of 38
-// planes a quarter of its rate (256^3, 4 bytes: 4.0 against 5.0 TB/s). Because a
-// block owns complete rows, every push can be written aligned: the value a lane stores at
-// x comes from the source node x - c_ix, one lane over (wave shuffle; the wave
-// edges through LDS, rows wrapping periodically inside the block). Psi of the
-// rows y-1 .. y+ROWS in planes z-1..z+1 is staged in LDS.
+// ROWS whole x-rows of one z-plane (NXT = nx nodes each). HBM bounds it: pushes
+// shifted by one node cost a plain push of 38 planes a fifth of its rate (256^3,
+// 4 bytes: 4.0 against 5.0 TB/s). Because a block owns complete rows, every push
+// can be written aligned: the value a lane stores at x comes from the source node
+// x - c_ix, one lane over (wave shuffle; the wave edges through LDS, rows
+// wrapping periodically inside the block). Psi of the rows y-1 .. y+ROWS in planes
+// z-1..z+1 is staged in LDS.
 template <class P, int NXT, int ROWS>
 __global__ __launch_bounds__(NXT * ROWS, NXT * ROWS == 256 ? (sizeof(typename P::R) == 8 ? 3 : 4) : 1) void k_fused_rows(
     Box bx, const typename P::S* __restrict__ fs, typename P::S* __restrict__ fd,
@@ -1091,9 +1092,9 @@ Tiles fused_tiles(int nx, int ny, bool solids, int precision) {
     }
     // FP32 without solids: the other rows of a multiple of 64 nodes are a tile each
     // (192 to 448 threads). The arithmetic stays the tile kernel's, bit for bit,
-    // and the shifted pushes of a row end in the block that began it: 192^3 0.429
-    // against 0.454 ms in tiles of 64 x 4, 384 x 128 x 96 0.291 against 0.348,
-    // 320 x 128 x 96 0.230 against 0.239. Not FP64 (192^3: 0.951 against 0.880 ms,
+    // and the shifted pushes of a row end in the block that began it: 192^3 0.426
+    // against 0.453 ms in tiles of 64 x 4, 384 x 128 x 96 0.292 against 0.350,
+    // 320 x 128 x 96 0.233 against 0.241, 448 x 128 x 96 0.330 against 0.341. Not FP64 (192^3: 0.951 against 0.880 ms,
     // 384: 0.651 against 0.610) or FP16 (192^3: 0.256 against 0.235).
     if (!solids && precision == LB_FP32 && nx > 128 && nx < 512 && nx % 64 == 0)
         t.BX = nx;

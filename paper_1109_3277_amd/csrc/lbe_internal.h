@@ -175,8 +175,8 @@ hipError_t launch_fold_impulses(lb_handle* h);
 // The step in moments (lbe_moment.hip).
 // A handle advances in moments where the collision leaves nothing else of a node
 // (tau = 1) and its arithmetic is FP64 (lbe_moment.h says why not the others):
-// 128^3 without particles 0.390 -> 0.092 ms a step, 512 x 512 x 320 with 25 k
-// ellipsoids 19.4 -> 8.3 ms.
+// 128^3 without particles 0.390 -> 0.081 ms a step, 512 x 512 x 320 with 25 k
+// ellipsoids 19.4 -> 7.1 ms.
 inline bool in_moments(const lb_params& p) { return p.tau == 1.0 && p.precision == LB_FP64; }
 size_t moment_bytes(const lb_params* p);  // one copy of the moment state
 constexpr int kMomTileX = 32;             // columns of the moment step: 32 x 8 nodes

@@ -1,9 +1,10 @@
 // The step at tau = 1 in moments (gfx950, FP64): see lbe_moment.h for the state.
 //
-// k_mstep advances the fluid by one whole step in one pass: it reads the seven
-// numbers of every node once and writes the next seven once (112 B per node and
-// step, against 928 B when populations are streamed and re-read for the
-// densities).
+// k_mstep advances the fluid by one whole step in one pass over the seven numbers of
+// every node: 112 B per node and step at the least, where populations that are
+// streamed and re-read for the densities take 928. It moves 1.7 to 1.8 times that:
+// a block of 32 x 8 nodes reads rho and u' at 340 positions of a plane and Psi at 432,
+// and three planes more than it writes.
 #include <algorithm>
 #include <type_traits>
 

@@ -364,8 +364,8 @@ int lb_add_ellipsoids(lb_handle* h, int32_t n, const double* radii, const double
         if (delta_rho && !isfinite(delta_rho[k])) return fail(h, LB_EINVAL, "non-finite delta_rho");
         if (density && !(density[k] > 0.0 && isfinite(density[k]))) return fail(h, LB_EINVAL, "density must be > 0");
     }
-    // pending kill/fill impulses move into the particle table before the
-    // partial-slot layout (set by the largest radius) can change
+    // pending kill/fill impulses move into the particle table before the layout of
+    // their slots (by particle and share: particle_split) changes with the count
     LBE_HIP(h, launch_fold_impulses(h));
     // plain form first: the removal below clears every solid node's slots,
     // where bounced populations of fluid neighbours may sit

@@ -124,6 +124,33 @@ def test_tuning_before_the_first_step_and_particles_after_it():
     b.close()
 
 
+def test_states_set_again_at_an_odd_step():
+    """Fields, a checkpoint and a body force set on single systems of a batch whose
+    copies stand at the odd parity."""
+    specs = _specs((1.0, 1.25, 1.0, 1.25), (34, 22, 25))
+    log(f"case set again {[(s['dims'], s['tau']) for s in specs]}")
+    b, lone = _batch(specs), [_lone(s) for s in specs]
+    early = [g.save_state() for g in lone]
+    b.step(3)
+    for k, g in enumerate(lone):
+        g.step(3)
+        for h in (b[k], g):
+            if k in (0, 1):
+                h.init_fields(specs[k]["rb"], specs[k]["ra"], np.tile([0.01, -0.02, 0.005], (h.N, 1)))
+            else:
+                h.load_state(early[k])
+                h.set_body_accel((0.0, 3e-5, -1e-5))
+        _same(b[k], g, f"system {k} set again")
+        assert _image(b[k]) == _image(g), k
+    for n in (2, 3):
+        b.step(n)
+        for k, g in enumerate(lone):
+            g.step(n)
+            _same(b[k], g, f"system {k}")
+            assert _image(b[k]) == _image(g), k
+    b.close()
+
+
 def test_tune_cache_keeps_the_two_paths_apart():
     """Boxes and solids alike, one batch in moments and one in populations: each
     is timed for its own kernel, and only a batch of the same kind takes its
