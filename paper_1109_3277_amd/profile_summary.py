@@ -3,6 +3,7 @@
     python paper_1109_3277_amd/profile_summary.py trace  <trace_dir> --title T --cmd C [--by-grid] > out.md
     python paper_1109_3277_amd/profile_summary.py traffic <fetch_dir> <write_dir> --kernel K \
         --workload W --precision P --nodes N --bytes-per-node B --cmds C1 C2 > out.md  (+ --json out.json)
+    python paper_1109_3277_amd/profile_summary.py units <counter_dir> --title T --cmd C > out.md
 
 `trace` reads the kernel statistics CSV of a `rocprofv3 --kernel-trace --stats`
 run and tabulates calls and average / min / max duration per kernel.
@@ -14,6 +15,11 @@ counter readings give the factor from counter units to bytes; every kernel's
 per-dispatch readings are scaled by it. The JSON record carries the hash of the
 fused kernel's sources (its file and the headers that it includes), so that a
 reader can tell whether it still describes the current kernel.
+
+`units` reads one `rocprofv3 --pmc` run with the counters of UNITS and gives, per
+kernel, the share of the SIMDs' cycles in which vector instructions execute, of
+the CUs' cycles in which LDS instructions do, and of LDS cycles lost to bank
+conflicts, with the instructions per wave.
 """
 from __future__ import annotations
 
@@ -166,6 +172,37 @@ def traffic(args):
         json.dump(rec, open(args.json, "w"), indent=1)
 
 
+UNITS = ["SQ_ACTIVE_INST_VALU", "SQ_ACTIVE_INST_LDS", "SQ_LDS_BANK_CONFLICT", "SQ_INSTS_VALU", "SQ_INSTS_LDS",
+         "SQ_WAVES", "SQ_BUSY_CU_CYCLES", "GRBM_GUI_ACTIVE"]
+CUS, SIMDS, XCDS = 256, 1024, 8
+
+
+def units(args):
+    data = {c: _counter(args.dir, c) for c in UNITS}
+    print(f"# {args.title}\n")
+    print("Command (from the repository root, on one MI355X):\n")
+    print(f"    {args.cmd}\n")
+    print("Means per dispatch. VALU: 4 SQ_ACTIVE_INST_VALU per SIMD and active cycle (GRBM_GUI_ACTIVE of an XCD). "
+          "LDS: 4 SQ_ACTIVE_INST_LDS per CU and active cycle. Conflicts: SQ_LDS_BANK_CONFLICT per CU and active "
+          "cycle.\n")
+    print("| kernel | dispatches | active cycles | VALU % | LDS % | bank conflicts % | VALU / wave | LDS / wave |")
+    print("|---|---|---|---|---|---|---|---|")
+    rows = []
+    for k, act in data["GRBM_GUI_ACTIVE"].items():
+        m = {c: sum(d.get(k, [0.0])) / max(len(d.get(k, [0.0])), 1) for c, d in data.items()}
+        cyc = m["GRBM_GUI_ACTIVE"] / XCDS
+        if cyc * len(act) < args.min_cycles:
+            continue
+        w = max(m["SQ_WAVES"], 1.0)
+        rows.append((cyc * len(act), f"| {k} | {len(act)} | {cyc:.0f} | "
+                     f"{100 * 4 * m['SQ_ACTIVE_INST_VALU'] / SIMDS / cyc:.1f} | "
+                     f"{100 * 4 * m['SQ_ACTIVE_INST_LDS'] / CUS / cyc:.1f} | "
+                     f"{100 * m['SQ_LDS_BANK_CONFLICT'] / CUS / cyc:.1f} | {m['SQ_INSTS_VALU'] / w:.0f} | "
+                     f"{m['SQ_INSTS_LDS'] / w:.0f} |"))
+    for _, line in sorted(rows, reverse=True):
+        print(line)
+
+
 def main():
     ap = argparse.ArgumentParser()
     sub = ap.add_subparsers(dest="what", required=True)
@@ -186,8 +223,13 @@ def main():
     p.add_argument("--copy-bytes", type=int, default=1 << 30)
     p.add_argument("--cmds", nargs=2, required=True)
     p.add_argument("--json")
+    u = sub.add_parser("units")
+    u.add_argument("dir")
+    u.add_argument("--title", required=True)
+    u.add_argument("--cmd", required=True)
+    u.add_argument("--min-cycles", type=float, default=1e5, help="omit kernels with fewer active cycles in all")
     a = ap.parse_args()
-    trace(a) if a.what == "trace" else traffic(a)
+    {"trace": trace, "traffic": traffic, "units": units}[a.what](a)
 
 
 if __name__ == "__main__":
